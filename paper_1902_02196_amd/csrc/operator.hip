@@ -177,8 +177,10 @@ __host__ __device__ __forceinline__ double2 green(double r, double k0) {
     return make_double2(c * a, -s * a);
 }
 
-__host__ __device__ double2 integrate_geometry(const AssemblyTables& T, const AxisKernel* kx[3], const int slot[3],
-                                      const int d[3], int order_far) {
+// Work item tid's share (points tid, tid + nthr, ...) of the quadrature of
+// one geometry: a density or point-mass slot per axis at offset d.
+__device__ double2 integrate_geometry(const AssemblyTables& T, const AxisKernel* kx[3], const int slot[3],
+                                      const int d[3], int order_far, int tid, int nthr) {
     const double* D = T.D;
     // singular corner: w* = -d Delta, touching when each axis reaches it
     bool touch = true;
@@ -211,39 +213,35 @@ __host__ __device__ double2 integrate_geometry(const AssemblyTables& T, const Ax
         double lo[3];
         for (int i = 0; i < 3; ++i) lo[i] = (slot[i] == 0) ? -D[i] : 0.0;
         if (nd == 3) {
-            for (int a = 0; a < n; ++a) {
+            for (int q = tid; q < n * n * n; q += nthr) {
+                const int a = q / (n * n), b = (q / n) % n, c = q % n;
                 const double wx = lo[0] + D[0] * gx[a];
                 const double fx = slot_value(*kx[0], slot[0], wx) * gw[a] * D[0];
                 const double rx = off[0] + wx;
-                for (int b = 0; b < n; ++b) {
-                    const double wy = lo[1] + D[1] * gx[b];
-                    const double fy = fx * slot_value(*kx[1], slot[1], wy) * gw[b] * D[1];
-                    const double ry = off[1] + wy;
-                    for (int c = 0; c < n; ++c) {
-                        const double wz = lo[2] + D[2] * gx[c];
-                        const double f = fy * slot_value(*kx[2], slot[2], wz) * gw[c] * D[2];
-                        const double rz = off[2] + wz;
-                        const double2 g = green(sqrt(rx * rx + ry * ry + rz * rz), T.k0);
-                        acc.x += f * g.x;
-                        acc.y += f * g.y;
-                    }
-                }
+                const double wy = lo[1] + D[1] * gx[b];
+                const double fy = fx * slot_value(*kx[1], slot[1], wy) * gw[b] * D[1];
+                const double ry = off[1] + wy;
+                const double wz = lo[2] + D[2] * gx[c];
+                const double f = fy * slot_value(*kx[2], slot[2], wz) * gw[c] * D[2];
+                const double rz = off[2] + wz;
+                const double2 g = green(sqrt(rx * rx + ry * ry + rz * rz), T.k0);
+                acc.x += f * g.x;
+                acc.y += f * g.y;
             }
         } else {
             const int i0 = dens[0], i1 = dens[1];
             const double rp = off[pt_axis] + base[pt_axis];
-            for (int a = 0; a < n; ++a) {
+            for (int q = tid; q < n * n; q += nthr) {
+                const int a = q / n, b = q % n;
                 const double w0 = lo[i0] + D[i0] * gx[a];
                 const double f0 = slot_value(*kx[i0], slot[i0], w0) * gw[a] * D[i0] * wfix;
                 const double r0 = off[i0] + w0;
-                for (int b = 0; b < n; ++b) {
-                    const double w1 = lo[i1] + D[i1] * gx[b];
-                    const double f = f0 * slot_value(*kx[i1], slot[i1], w1) * gw[b] * D[i1];
-                    const double r1 = off[i1] + w1;
-                    const double2 g = green(sqrt(r0 * r0 + r1 * r1 + rp * rp), T.k0);
-                    acc.x += f * g.x;
-                    acc.y += f * g.y;
-                }
+                const double w1 = lo[i1] + D[i1] * gx[b];
+                const double f = f0 * slot_value(*kx[i1], slot[i1], w1) * gw[b] * D[i1];
+                const double r1 = off[i1] + w1;
+                const double2 g = green(sqrt(r0 * r0 + r1 * r1 + rp * rp), T.k0);
+                acc.x += f * g.x;
+                acc.y += f * g.y;
             }
         }
         return acc;
@@ -266,50 +264,40 @@ __host__ __device__ double2 integrate_geometry(const AssemblyTables& T, const Ax
     if (nd == 3) {
         const double jac0 = D[0] * D[1] * D[2];
         for (int k = 0; k < 3; ++k) {
-            const int j1 = (k + 1) % 3, j2 = (k + 2) % 3;
-            for (int a = 0; a < n; ++a) {
-                const double s = gx[a];
-                for (int b = 0; b < n; ++b) {
-                    const double t1 = gx[b];
-                    for (int c = 0; c < n; ++c) {
-                        const double t2 = gx[c];
-                        double xi[3];
-                        xi[k] = s;
-                        xi[j1] = s * t1;
-                        xi[j2] = s * t2;
-                        double w[3], rr = 0, f = gw[a] * gw[b] * gw[c] * s * s * jac0;
-                        for (int i = 0; i < 3; ++i) {
-                            w[i] = corner[i] + ext[i] * xi[i];
-                            const double ri = off[i] + w[i];
-                            rr += ri * ri;
-                            f *= slot_value(*kx[i], slot[i], w[i]);
-                        }
-                        const double2 g = green(sqrt(rr), T.k0);
-                        acc.x += f * g.x;
-                        acc.y += f * g.y;
-                    }
+            for (int q = tid; q < n * n * n; q += nthr) {
+                const int a = q / (n * n), b = (q / n) % n, c = q % n;
+                const double s = gx[a], st1 = s * gx[b], st2 = s * gx[c];
+                double rr = 0, f = gw[a] * gw[b] * gw[c] * s * s * jac0;
+                for (int i = 0; i < 3; ++i) {
+                    // xi_k = s, the next axis s t1, the one after s t2
+                    const double xi = i == k ? s : (i == (k + 1) % 3 ? st1 : st2);
+                    const double w = corner[i] + ext[i] * xi;
+                    const double ri = off[i] + w;
+                    rr += ri * ri;
+                    f *= slot_value(*kx[i], slot[i], w);
                 }
+                const double2 g = green(sqrt(rr), T.k0);
+                acc.x += f * g.x;
+                acc.y += f * g.y;
             }
         }
     } else {
         const int i0 = dens[0], i1 = dens[1];
         const double jac0 = D[i0] * D[i1] * wfix;
         for (int k = 0; k < 2; ++k) {
-            for (int a = 0; a < n; ++a) {
-                const double s = gx[a];
-                for (int b = 0; b < n; ++b) {
-                    const double t = gx[b];
-                    const double xi0 = (k == 0) ? s : s * t;
-                    const double xi1 = (k == 0) ? s * t : s;
-                    const double w0 = corner[i0] + ext[i0] * xi0;
-                    const double w1 = corner[i1] + ext[i1] * xi1;
-                    const double r0 = off[i0] + w0, r1 = off[i1] + w1;
-                    const double f = gw[a] * gw[b] * s * jac0 * slot_value(*kx[i0], slot[i0], w0) *
-                                     slot_value(*kx[i1], slot[i1], w1);
-                    const double2 g = green(sqrt(r0 * r0 + r1 * r1), T.k0);
-                    acc.x += f * g.x;
-                    acc.y += f * g.y;
-                }
+            for (int q = tid; q < n * n; q += nthr) {
+                const int a = q / n, b = q % n;
+                const double s = gx[a], t = gx[b];
+                const double xi0 = (k == 0) ? s : s * t;
+                const double xi1 = (k == 0) ? s * t : s;
+                const double w0 = corner[i0] + ext[i0] * xi0;
+                const double w1 = corner[i1] + ext[i1] * xi1;
+                const double r0 = off[i0] + w0, r1 = off[i1] + w1;
+                const double f = gw[a] * gw[b] * s * jac0 * slot_value(*kx[i0], slot[i0], w0) *
+                                 slot_value(*kx[i1], slot[i1], w1);
+                const double2 g = green(sqrt(r0 * r0 + r1 * r1), T.k0);
+                acc.x += f * g.x;
+                acc.y += f * g.y;
             }
         }
     }
@@ -379,55 +367,6 @@ FarTables build_far_tables(const AssemblyTables& T) {
         }
     }
     return F;
-}
-
-// The separable sum of one offset evaluated serially (host reference of the
-// parallel kernel below; same grid, same contraction order).
-void assemble_far_serial(const FarTables& F, const AssemblyTables& T, int b, const int d[3], double2* out60) {
-    const FarBand& B = F.band[b];
-    const int P = B.P;
-    std::vector<double2> S(F.nterm, make_double2(0, 0)), t1(P * 16), t2(F.npair);
-    std::vector<double2> slab(P * P);
-    for (int i = 0; i < P; ++i) {
-        const double rx = d[0] * T.D[0] + B.w[0][i];
-        for (int j = 0; j < P; ++j)
-            for (int k = 0; k < P; ++k) {
-                const double ry = d[1] * T.D[1] + B.w[1][j], rz = d[2] * T.D[2] + B.w[2][k];
-                slab[j * P + k] = (B.ispt[i] + B.ispt[j] + B.ispt[k] > 1)
-                                      ? make_double2(0, 0)
-                                      : green(sqrt(rx * rx + ry * ry + rz * rz), T.k0);
-            }
-        for (int j = 0; j < P; ++j)
-            for (int kz = 0; kz < 16; ++kz) {
-                double2 a = make_double2(0, 0);
-                for (int k = 0; k < P; ++k) {
-                    a.x += B.W[2][kz][k] * slab[j * P + k].x;
-                    a.y += B.W[2][kz][k] * slab[j * P + k].y;
-                }
-                t1[j * 16 + kz] = a;
-            }
-        for (int p = 0; p < F.npair; ++p) {
-            double2 a = make_double2(0, 0);
-            for (int j = 0; j < P; ++j) {
-                a.x += B.W[1][F.pair_ky[p]][j] * t1[j * 16 + F.pair_kz[p]].x;
-                a.y += B.W[1][F.pair_ky[p]][j] * t1[j * 16 + F.pair_kz[p]].y;
-            }
-            t2[p] = a;
-        }
-        for (int t = 0; t < F.nterm; ++t) {
-            const double wx = B.W[0][F.term_kx[t]][i];
-            S[t].x += wx * t2[F.term_pair[t]].x;
-            S[t].y += wx * t2[F.term_pair[t]].y;
-        }
-    }
-    for (int e = 0; e < F.nent; ++e) {
-        double2 a = make_double2(0, 0);
-        for (int t = F.ent_first[e]; t < F.ent_first[e] + F.ent_count[e]; ++t) {
-            a.x += F.term_coef[t] * S[t].x;
-            a.y += F.term_coef[t] * S[t].y;
-        }
-        out60[e] = a;
-    }
 }
 
 // One wavefront per offset (grid-stride over the offsets of the cube that
@@ -523,10 +462,24 @@ __global__ void __launch_bounds__(64) k_assemble_far(double2* __restrict__ out, 
     }
 }
 
-// N^{e}(d) for one unique entry and one offset d >= 0
-__host__ __device__ double2 assemble_entry(const AssemblyTables& T, int e, const int d[3]) {
-    const int dinf = max(d[0], max(d[1], d[2]));
-    const int nfar = far_order(dinf, T.order_near);
+// Entry-by-entry assembly of the offsets at the singular corner, d in
+// {0, 1}^3 (those may touch the singular point; Duffy rules): one workgroup
+// per (entry, offset), the quadrature points of every geometry dealt to its
+// work items and their partial sums added in a fixed order.  Bound by the
+// FP64 Green's function (sqrt, sincos) of up to 40k points per entry and
+// offset: 0.36 ms on any grid; one work item per (entry, offset) ran the
+// points in series for 75 ms, most of a 64^3 set-up.
+constexpr int kNearThreads = 256;
+
+__global__ void __launch_bounds__(kNearThreads) k_assemble_near(double2* __restrict__ out,
+                                                                const AssemblyTables* __restrict__ Tg, int Nx, int Ny,
+                                                                int Nz) {
+    const AssemblyTables& T = *Tg;
+    const long long V = (long long)Nx * Ny * Nz;
+    const int e = blockIdx.x, c = blockIdx.y, tid = threadIdx.x;
+    const int d[3] = {c & 1, (c >> 1) & 1, c >> 2};
+    if (d[0] >= Nx || d[1] >= Ny || d[2] >= Nz) return;   // uniform over the workgroup
+    const int nfar = far_order(max(d[0], max(d[1], d[2])), T.order_near);
     const EntryTerms& E = T.ent[e];
     double2 acc = make_double2(0, 0);
     for (int t = 0; t < E.nterm; ++t) {
@@ -541,7 +494,7 @@ __host__ __device__ double2 assemble_entry(const AssemblyTables& T, int e, const
                     if (!slot_used(*kx[2], slot[2])) continue;
                     const int npt = (slot[0] >= 2) + (slot[1] >= 2) + (slot[2] >= 2);
                     if (npt > 1) continue;  // does not occur for these measures
-                    const double2 g = integrate_geometry(T, kx, slot, d, nfar);
+                    const double2 g = integrate_geometry(T, kx, slot, d, nfar, tid, kNearThreads);
                     part.x += g.x;
                     part.y += g.y;
                 }
@@ -550,21 +503,21 @@ __host__ __device__ double2 assemble_entry(const AssemblyTables& T, int e, const
         acc.x += E.coef[t] * part.x;
         acc.y += E.coef[t] * part.y;
     }
-    if (d[0] == 0 && d[1] == 0 && d[2] == 0 && E.gram_l >= 0) acc.x += T.gram[E.gram_l];
-    return acc;
-}
-
-// entry-by-entry assembly of the offsets at the singular corner,
-// d in {0, 1}^3 (those may touch the singular point; Duffy rules)
-__global__ void __launch_bounds__(64) k_assemble_near(double2* __restrict__ out, const AssemblyTables* __restrict__ Tg,
-                                                      int Nx, int Ny, int Nz) {
-    const long long V = (long long)Nx * Ny * Nz;
-    const int e = blockIdx.x;
-    const int c = threadIdx.x;
-    if (c >= 8) return;
-    const int d[3] = {c & 1, (c >> 1) & 1, c >> 2};
-    if (d[0] >= Nx || d[1] >= Ny || d[2] >= Nz) return;
-    out[(long long)e * V + ((long long)d[2] * Ny + d[1]) * Nx + d[0]] = assemble_entry(*Tg, e, d);
+    __shared__ double2 sum[kNearThreads];
+    sum[tid] = acc;
+    __syncthreads();
+    for (int h = kNearThreads / 2; h > 0; h /= 2) {
+        if (tid < h) {
+            sum[tid].x += sum[tid + h].x;
+            sum[tid].y += sum[tid + h].y;
+        }
+        __syncthreads();
+    }
+    if (tid == 0) {
+        double2 v = sum[0];
+        if (c == 0 && E.gram_l >= 0) v.x += T.gram[E.gram_l];
+        out[(long long)e * V + ((long long)d[2] * Ny + d[1]) * Nx + d[0]] = v;
+    }
 }
 
 // circulant embedding of one unique entry on the M grid ([Mz][My][Mx]):
@@ -621,7 +574,7 @@ void assemble_blocks(double2* out, const AssemblyTables& T, int Nx, int Ny, int 
     VIE_HIP(hipMemcpyAsync(dT, &T, sizeof(AssemblyTables), hipMemcpyHostToDevice, s));
     VIE_HIP(hipMemcpyAsync(dF, &F, sizeof(FarTables), hipMemcpyHostToDevice, s));
     const long long V = (long long)Nx * Ny * Nz;
-    hipLaunchKernelGGL(k_assemble_near, dim3(T.nent), dim3(64), 0, s, out, dT, Nx, Ny, Nz);
+    hipLaunchKernelGGL(k_assemble_near, dim3(T.nent, 8), dim3(kNearThreads), 0, s, out, dT, Nx, Ny, Nz);
     VIE_HIP(hipGetLastError());
     const int dmax = std::max(Nx, std::max(Ny, Nz)) - 1;
     for (int b = 0; b < kFarBands; ++b) {
