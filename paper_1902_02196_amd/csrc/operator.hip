@@ -369,20 +369,28 @@ FarTables build_far_tables(const AssemblyTables& T) {
     return F;
 }
 
-// One wavefront per offset (grid-stride over the offsets of the cube that
-// holds the band, those below the band skipped).  Per x abscissa: the (y, z) slab of Green's values, the z
-// contraction for all 16 kernel pairs, the y contraction for the (ky, kz)
-// pairs in use, and the x accumulation of every (entry, term) sum.
-template <int P>
-__global__ void __launch_bounds__(64) k_assemble_far(double2* __restrict__ out, const FarTables* __restrict__ Fg,
-                                                     int b, double Dx, double Dy, double Dz, double k0, int Nx,
-                                                     int Ny, int Nz, int cx, int cy, int cz) {
-    __shared__ double2 slab[P * P];
-    __shared__ double2 t1[P * 16];
-    __shared__ double2 t2[kFarTerms];
+// One workgroup of W wavefronts per offset (grid-stride over the offsets of
+// the cube that holds the band, those below the band skipped); wavefront w
+// takes the x abscissae w, w + W, ...  Per x abscissa: the (y, z) slab of
+// Green's values, the z contraction for all 16 kernel pairs, the y
+// contraction for the (ky, kz) pairs in use, and the x accumulation of every
+// (entry, term) sum; the wavefronts' sums are added in order at the end.
+// W = 4 for the near bands, whose 19, 98 and 604 offsets leave most of the
+// chip idle and wait on one wavefront's serial chain (270, 76 and 74 us; 576, 326 and 199 us
+// with W = 1); the far bands have thousands of offsets and take W = 1.
+template <int P, int W>
+__global__ void __launch_bounds__(64 * W) k_assemble_far(double2* __restrict__ out, const FarTables* __restrict__ Fg,
+                                                         int b, double Dx, double Dy, double Dz, double k0, int Nx,
+                                                         int Ny, int Nz, int cx, int cy, int cz) {
+    __shared__ double2 slab_[W][P * P];
+    __shared__ double2 t1_[W][P * 16];
+    __shared__ double2 t2_[W][kFarTerms];
     const FarTables& F = *Fg;
     const FarBand& B = F.band[b];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double2* slab = slab_[w];
+    double2* t1 = t1_[w];
+    double2* t2 = t2_[w];
     const long long V = (long long)Nx * Ny * Nz;
     const int nterm = F.nterm, npair = F.npair;
     // offsets of the band lie in the cube [0, cx) x [0, cy) x [0, cz)
@@ -393,52 +401,60 @@ __global__ void __launch_bounds__(64) k_assemble_far(double2* __restrict__ out, 
         const int dinf = max(d0, max(d1, d2));
         if (dinf < B.dlo || dinf > B.dhi) continue;   // uniform over the workgroup
         double2 s0 = make_double2(0, 0), s1 = make_double2(0, 0);   // terms tid, tid + 64
-        for (int i = 0; i < P; ++i) {
-            const double rx = d0 * Dx + B.w[0][i];
-            const int pi = B.ispt[i];
-            for (int idx = tid; idx < P * P; idx += 64) {
-                const int j = idx / P, k = idx - j * P;
-                double2 g = make_double2(0, 0);
-                if (pi + B.ispt[j] + B.ispt[k] <= 1) {
-                    const double ry = d1 * Dy + B.w[1][j], rz = d2 * Dz + B.w[2][k];
-                    g = green(sqrt(rx * rx + ry * ry + rz * rz), k0);
+        // every wavefront runs every round (barriers); one past the last
+        // abscissa has nothing to add
+        for (int i0 = 0; i0 < P; i0 += W) {
+            const int i = i0 + w;
+            const bool act = i < P;
+            if (act) {
+                const double rx = d0 * Dx + B.w[0][i];
+                const int pi = B.ispt[i];
+                for (int idx = tid; idx < P * P; idx += 64) {
+                    const int j = idx / P, k = idx - j * P;
+                    double2 g = make_double2(0, 0);
+                    if (pi + B.ispt[j] + B.ispt[k] <= 1) {
+                        const double ry = d1 * Dy + B.w[1][j], rz = d2 * Dz + B.w[2][k];
+                        g = green(sqrt(rx * rx + ry * ry + rz * rz), k0);
+                    }
+                    slab[idx] = g;
                 }
-                slab[idx] = g;
             }
             __syncthreads();
-            for (int idx = tid; idx < P * 16; idx += 64) {
-                const int j = idx >> 4, kz = idx & 15;
-                const double* wz = B.W[2][kz];
-                double2 a = make_double2(0, 0);
+            if (act)
+                for (int idx = tid; idx < P * 16; idx += 64) {
+                    const int j = idx >> 4, kz = idx & 15;
+                    const double* wz = B.W[2][kz];
+                    double2 a = make_double2(0, 0);
 #pragma unroll
-                for (int k = 0; k < P; ++k) {
-                    const double2 g = slab[j * P + k];
-                    a.x += wz[k] * g.x;
-                    a.y += wz[k] * g.y;
+                    for (int k = 0; k < P; ++k) {
+                        const double2 g = slab[j * P + k];
+                        a.x += wz[k] * g.x;
+                        a.y += wz[k] * g.y;
+                    }
+                    t1[idx] = a;
                 }
-                t1[idx] = a;
-            }
             __syncthreads();
-            for (int p = tid; p < npair; p += 64) {
-                const double* wy = B.W[1][F.pair_ky[p]];
-                const int kz = F.pair_kz[p];
-                double2 a = make_double2(0, 0);
+            if (act)
+                for (int p = tid; p < npair; p += 64) {
+                    const double* wy = B.W[1][F.pair_ky[p]];
+                    const int kz = F.pair_kz[p];
+                    double2 a = make_double2(0, 0);
 #pragma unroll
-                for (int j = 0; j < P; ++j) {
-                    const double2 u = t1[j * 16 + kz];
-                    a.x += wy[j] * u.x;
-                    a.y += wy[j] * u.y;
+                    for (int j = 0; j < P; ++j) {
+                        const double2 u = t1[j * 16 + kz];
+                        a.x += wy[j] * u.x;
+                        a.y += wy[j] * u.y;
+                    }
+                    t2[p] = a;
                 }
-                t2[p] = a;
-            }
             __syncthreads();
-            if (tid < nterm) {
+            if (act && tid < nterm) {
                 const double wx = B.W[0][F.term_kx[tid]][i];
                 const double2 u = t2[F.term_pair[tid]];
                 s0.x += wx * u.x;
                 s0.y += wx * u.y;
             }
-            if (tid + 64 < nterm) {
+            if (act && tid + 64 < nterm) {
                 const double wx = B.W[0][F.term_kx[tid + 64]][i];
                 const double2 u = t2[F.term_pair[tid + 64]];
                 s1.x += wx * u.x;
@@ -450,12 +466,13 @@ __global__ void __launch_bounds__(64) k_assemble_far(double2* __restrict__ out, 
         if (tid < nterm) t2[tid] = s0;
         if (tid + 64 < nterm) t2[tid + 64] = s1;
         __syncthreads();
-        if (tid < F.nent) {
+        if (w == 0 && tid < F.nent) {
             double2 a = make_double2(0, 0);
-            for (int t = F.ent_first[tid]; t < F.ent_first[tid] + F.ent_count[tid]; ++t) {
-                a.x += F.term_coef[t] * t2[t].x;
-                a.y += F.term_coef[t] * t2[t].y;
-            }
+            for (int t = F.ent_first[tid]; t < F.ent_first[tid] + F.ent_count[tid]; ++t)
+                for (int u = 0; u < W; ++u) {
+                    a.x += F.term_coef[t] * t2_[u][t].x;
+                    a.y += F.term_coef[t] * t2_[u][t].y;
+                }
             out[(long long)tid * V + v] = a;
         }
         __syncthreads();
@@ -587,17 +604,17 @@ void assemble_blocks(double2* out, const AssemblyTables& T, int Nx, int Ny, int 
                               (long long)std::min(B.dlo, Nx) * std::min(B.dlo, Ny) * std::min(B.dlo, Nz);
         const unsigned grid = (unsigned)std::max<long long>(1, std::min<long long>(cnt, 1 << 16));
         const double* D = T.D;
-#define FAR_CASE(P_)                                                                                        \
-    case P_:                                                                                                \
-        hipLaunchKernelGGL(k_assemble_far<P_>, dim3(grid), dim3(64), 0, s, out, dF, b, D[0], D[1], D[2], T.k0, \
-                           Nx, Ny, Nz, cx, cy, cz);                                                         \
+#define FAR_CASE(P_, W_)                                                                                         \
+    case P_:                                                                                                     \
+        hipLaunchKernelGGL((k_assemble_far<P_, W_>), dim3(grid), dim3(64 * W_), 0, s, out, dF, b, D[0], D[1],    \
+                           D[2], T.k0, Nx, Ny, Nz, cx, cy, cz);                                                  \
         break;
         switch (B.P) {
-            FAR_CASE(31)
-            FAR_CASE(21)
-            FAR_CASE(17)
-            FAR_CASE(13)
-            FAR_CASE(11)
+            FAR_CASE(31, 4)
+            FAR_CASE(21, 4)
+            FAR_CASE(17, 4)
+            FAR_CASE(13, 1)
+            FAR_CASE(11, 1)
             default: throw Error(-1, "assembly: unsupported Gauss order band");
         }
 #undef FAR_CASE
