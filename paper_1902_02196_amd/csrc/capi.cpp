@@ -100,8 +100,9 @@ int vie_create(vie_ctx** out, int device, void* stream) {
 void vie_destroy(vie_ctx* ctx) {
     if (!ctx) return;
     (void)hipSetDevice(ctx->c.device);
-    if (ctx->c.stream) (void)hipStreamSynchronize(ctx->c.stream);
-    else (void)hipDeviceSynchronize();
+    // the null stream too: a device-wide synchronisation would break a graph
+    // capture under way in another thread
+    (void)hipStreamSynchronize(ctx->c.stream);
     delete ctx;
 }
 
@@ -160,16 +161,24 @@ int vie_set_grid(vie_ctx* ctx, int nx, int ny, int nz, double dx, double dy, dou
         c.V = (long long)nx * ny * nz;
         c.Osz = (long long)c.O[0] * c.O[1] * c.O[2];
         auto opd = std::make_shared<OperatorData>();
+        // uploads go through the context's stream and end with the assembly's
+        // synchronisation: a blocking copy would break a graph capture under
+        // way in another thread
+        std::vector<double2> tws[3];
+        std::vector<float2> tws32[3];
         for (int i = 0; i < 3; ++i) {
             opd->ax[i].plan = make_plan(M[i]);
-            std::vector<double2> tw;
+            std::vector<double2>& tw = tws[i];
             make_twiddles(M[i], tw);
-            std::vector<float2> tw32(M[i]);
+            std::vector<float2>& tw32 = tws32[i];
+            tw32.resize(M[i]);
             for (int k = 0; k < M[i]; ++k) tw32[k] = make_float2((float)tw[k].x, (float)tw[k].y);
             VIE_HIP(hipMalloc(&opd->ax[i].tw128, M[i] * sizeof(double2)));
             VIE_HIP(hipMalloc(&opd->ax[i].tw64, M[i] * sizeof(float2)));
-            VIE_HIP(hipMemcpy(opd->ax[i].tw128, tw.data(), M[i] * sizeof(double2), hipMemcpyHostToDevice));
-            VIE_HIP(hipMemcpy(opd->ax[i].tw64, tw32.data(), M[i] * sizeof(float2), hipMemcpyHostToDevice));
+            VIE_HIP(hipMemcpyAsync(opd->ax[i].tw128, tw.data(), M[i] * sizeof(double2), hipMemcpyHostToDevice,
+                                   c.stream));
+            VIE_HIP(hipMemcpyAsync(opd->ax[i].tw64, tw32.data(), M[i] * sizeof(float2), hipMemcpyHostToDevice,
+                                   c.stream));
             opd->bytes += M[i] * (sizeof(double2) + sizeof(float2));
         }
         VIE_HIP(hipMalloc(&opd->T, 60 * c.V * sizeof(double2)));
@@ -187,9 +196,9 @@ int vie_set_grid(vie_ctx* ctx, int nx, int ny, int nz, double dx, double dy, dou
         // operator spectra
         const long long Mt = (long long)M[0] * M[1] * M[2];
         double2* circ = static_cast<double2*>(c.ws.get(Mt * sizeof(double2)));
-        const double2* tws[3] = {c.ax[0].tw128, c.ax[1].tw128, c.ax[2].tw128};
+        const double2* twd[3] = {c.ax[0].tw128, c.ax[1].tw128, c.ax[2].tw128};
         FftPlan plans[3] = {c.ax[0].plan, c.ax[1].plan, c.ax[2].plan};
-        embed_and_transform(c.U128, c.U64, c.T, circ, nx, ny, nz, M[0], M[1], M[2], plans, tws, c.stream);
+        embed_and_transform(c.U128, c.U64, c.T, circ, nx, ny, nz, M[0], M[1], M[2], plans, twd, c.stream);
         VIE_HIP(hipStreamSynchronize(c.stream));
     });
 }

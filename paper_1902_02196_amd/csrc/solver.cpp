@@ -294,19 +294,28 @@ static int run(Ctx& c, const vie_solve_opts& o, int nrhs, double2* x, const Layo
                 if (!c.graphs.cap) VIE_HIP(hipStreamCreateWithFlags(&c.graphs.cap, hipStreamNonBlocking));
                 const hipStream_t own = c.stream;
                 hipGraph_t gr = nullptr;
+                bool captured = true;
                 c.stream = c.graphs.cap;
-                VIE_HIP(hipStreamBeginCapture(c.stream, hipStreamCaptureModeThreadLocal));
-                try {
-                    run_steps();
-                } catch (...) {
-                    (void)hipStreamEndCapture(c.stream, &gr);
-                    if (gr) (void)hipGraphDestroy(gr);
-                    c.stream = own;
-                    throw;
+                if (hipStreamBeginCapture(c.stream, hipStreamCaptureModeThreadLocal) == hipSuccess) {
+                    try {
+                        run_steps();
+                    } catch (...) {
+                        captured = false;
+                    }
+                    if (hipStreamEndCapture(c.stream, &gr) != hipSuccess) captured = false;
+                } else {
+                    captured = false;
                 }
-                const hipError_t e = hipStreamEndCapture(c.stream, &gr);
                 c.stream = own;
-                VIE_HIP(e);
+                if (!captured) {
+                    // a device synchronisation or blocking copy of another
+                    // thread of the process breaks a capture: nothing has
+                    // run, so the steps are launched one by one this time
+                    if (gr) (void)hipGraphDestroy(gr);
+                    (void)hipGetLastError();
+                    run_steps();
+                    return;
+                }
                 hipGraphExec_t ex = nullptr;
                 const hipError_t ei = hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0);
                 (void)hipGraphDestroy(gr);

@@ -5,11 +5,14 @@ bricks with the three edges apart.
 Tolerance: each entry within 1e-10 of the largest entry of its offset, the
 accuracy of the two independent quadratures against each other.
 """
+import threading
+
 import numpy as np
 import pytest
 
+import vie_inputs as vi
 from oracle import physics, toeplitz
-from tests.layout import unique_from_octant
+from tests.layout import unique_from_octant, vox_to_lib
 
 pytestmark = pytest.mark.gpu
 
@@ -41,3 +44,44 @@ def test_assembly_on_degenerate_grids(vie, N, D):
             for ix in range(N[0]):
                 a, b = lib[:, iz, iy, ix], ref[:, iz, iy, ix]
                 assert np.abs(a - b).max() <= 1e-10 * np.abs(b).max(), (ix, iy, iz)
+
+
+def test_setup_beside_captured_solves(vie):
+    """Graph captures of one thread's solves and the grid set-ups of another
+    do not disturb each other: every call succeeds, every solution has the
+    same bits."""
+    import torch
+    N, D = (6, 6, 6), (0.005,) * 3
+    e, s = (vox_to_lib(v) for v in vi.sphere(N, D, 0.012, 50.0, 0.7))
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    a, b = (vie.Context(0, st) for st in streams)
+    a.set_grid(N, D, F)
+    a.set_contrast(e, s)
+    et = torch.empty(a.vec_shape(1), dtype=torch.complex128, device="cuda")
+    x = torch.empty_like(et)
+    a.incident_planewave(et)
+    torch.cuda.synchronize()
+    stop, errors, sols = threading.Event(), [], []
+
+    def setups():
+        try:
+            while not stop.is_set():
+                b.set_grid((5, 4, 6), D, F)
+        except Exception as err:   # reported by the test
+            errors.append(err)
+
+    t = threading.Thread(target=setups)
+    t.start()
+    try:
+        for _ in range(30):
+            a.set_contrast(e, s)   # forgets the captured steps
+            for _ in range(3):     # plain, captured, replayed
+                code, _ = a.solve(et, x, mode=vie.SOLVE_FP32_IR, tol=1e-8, restart=12, graph=1)
+                assert code == vie.VIE_OK
+                with torch.cuda.stream(streams[0]):
+                    sols.append(x.cpu().numpy())
+    finally:
+        stop.set()
+        t.join()
+    assert not errors, errors
+    assert all(np.array_equal(v, sols[0]) for v in sols)
