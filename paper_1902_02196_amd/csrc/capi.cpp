@@ -62,6 +62,15 @@ void Ctx::free_mcontrast() {
 
 }  // namespace vie
 
+// octant spectra of the context's 60 tensors, through the FFT workspace
+static void build_spectra(Ctx& c) {
+    const size_t bytes = spectra_scratch_bytes(c.N, c.M);
+    double2* scratch = static_cast<double2*>(c.ws.get(bytes));
+    const double2* tws[3] = {c.ax[0].tw128, c.ax[1].tw128, c.ax[2].tw128};
+    const FftPlan plans[3] = {c.ax[0].plan, c.ax[1].plan, c.ax[2].plan};
+    operator_spectra(c.U128, c.U64, c.T, scratch, bytes, c.N, c.M, plans, tws, c.stream);
+}
+
 static void check_ctx(vie_ctx* ctx) { VIE_REQUIRE(ctx != nullptr, VIE_EINVAL, "null context"); }
 
 static void set_device(Ctx& c) { VIE_HIP(hipSetDevice(c.device)); }
@@ -193,12 +202,7 @@ int vie_set_grid(vie_ctx* ctx, int nx, int ny, int nz, double dx, double dy, dou
         AssemblyTables tab = build_assembly_tables(c.D, c.k0);
         assemble_blocks(c.T, tab, nx, ny, nz, c.stream);
         c.has_grid = true;
-        // operator spectra
-        const long long Mt = (long long)M[0] * M[1] * M[2];
-        double2* circ = static_cast<double2*>(c.ws.get(Mt * sizeof(double2)));
-        const double2* twd[3] = {c.ax[0].tw128, c.ax[1].tw128, c.ax[2].tw128};
-        FftPlan plans[3] = {c.ax[0].plan, c.ax[1].plan, c.ax[2].plan};
-        embed_and_transform(c.U128, c.U64, c.T, circ, nx, ny, nz, M[0], M[1], M[2], plans, twd, c.stream);
+        build_spectra(c);
         VIE_HIP(hipStreamSynchronize(c.stream));
     });
 }
@@ -247,12 +251,7 @@ int vie_set_toeplitz(vie_ctx* ctx, const double* T_host) {
         VIE_REQUIRE(c.op.use_count() == 1, VIE_ESTATE, "the operator is shared with another context");
         VIE_REQUIRE(T_host != nullptr, VIE_EINVAL, "T_host is null");
         VIE_HIP(hipMemcpyAsync(c.T, T_host, 60 * c.V * sizeof(double2), hipMemcpyHostToDevice, c.stream));
-        const long long Mt = (long long)c.M[0] * c.M[1] * c.M[2];
-        double2* circ = static_cast<double2*>(c.ws.get(Mt * sizeof(double2)));
-        const double2* tws[3] = {c.ax[0].tw128, c.ax[1].tw128, c.ax[2].tw128};
-        FftPlan plans[3] = {c.ax[0].plan, c.ax[1].plan, c.ax[2].plan};
-        embed_and_transform(c.U128, c.U64, c.T, circ, c.N[0], c.N[1], c.N[2], c.M[0], c.M[1], c.M[2], plans, tws,
-                            c.stream);
+        build_spectra(c);
         VIE_HIP(hipStreamSynchronize(c.stream));
     });
 }
@@ -319,12 +318,7 @@ int vie_tucker_expand(vie_ctx* ctx) {
         VIE_REQUIRE(c.op.use_count() == 1, VIE_ESTATE, "the operator is shared with another context");
         // T <- T_hat, then the set-up's embedding, FFT and octant
         tucker_reconstruct(c, c.T);
-        const long long Mt = (long long)c.M[0] * c.M[1] * c.M[2];
-        double2* circ = static_cast<double2*>(c.ws.get(Mt * sizeof(double2)));
-        const double2* tws[3] = {c.ax[0].tw128, c.ax[1].tw128, c.ax[2].tw128};
-        FftPlan plans[3] = {c.ax[0].plan, c.ax[1].plan, c.ax[2].plan};
-        embed_and_transform(c.U128, c.U64, c.T, circ, c.N[0], c.N[1], c.N[2], c.M[0], c.M[1], c.M[2], plans, tws,
-                            c.stream);
+        build_spectra(c);
         VIE_HIP(hipStreamSynchronize(c.stream));
     });
 }

@@ -58,8 +58,6 @@ bool launch_strided_compiled(bool fwd, bool epi, const C<R>* in, C<R>* out, cons
 bool strided_ct_fits(int es, int n, int tile);
 bool strided_tile_ok(int es, int n, int tile);
 int strided_tile_for(int es, int n, int preferred);
-template <typename R>
-void launch_rows(bool fwd, C<R>* data, long long nrows, const FftPlan& plan, const C<R>* tw, hipStream_t s);
 
 // operator.hip
 AssemblyTables build_assembly_tables(const double D[3], double k0);
@@ -68,11 +66,13 @@ AssemblyTables build_curl_tables(const double D[3], double k0);
 void assemble_blocks(double2* out, const AssemblyTables& T, int Nx, int Ny, int Nz, hipStream_t s);
 int unique_refl_sign(int e, int axis);
 int curl_refl_sign(int e, int axis);
-// circulant embedding, 3-D FFT and octant [Oz][Oy][nent][Ox] of the 60 N
-// tensors, or of the 30 curl tensors (curl = true; U64 may be null)
-void embed_and_transform(double2* U128, float2* U64, const double2* T, double2* circ, int Nx, int Ny, int Nz,
-                         int Mx, int My, int Mz, const FftPlan plans[3], const double2* const tw[3], hipStream_t s,
-                         bool curl = false);
+// octant spectra [Oz][Oy][nent][Ox] of the circulant embeddings of the 60 N
+// tensors, or of the 30 curl tensors (curl = true; U64 may be null), through
+// a scratch buffer of at least one entry (spectra_scratch_bytes: the usual size)
+size_t spectra_scratch_bytes(const int N[3], const int M[3]);
+void operator_spectra(double2* U128, float2* U64, const double2* T, double2* scratch, size_t scratch_bytes,
+                      const int N[3], const int M[3], const FftPlan plans[3], const double2* const tw[3],
+                      hipStream_t s, bool curl = false);
 
 // setup.hip: materials, excitation, post-processing
 struct Materials {

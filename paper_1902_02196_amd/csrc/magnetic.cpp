@@ -21,7 +21,7 @@ void ensure_curl(Ctx& c) {
     OperatorData& op = *c.op;
     std::lock_guard<std::mutex> g(op.curl_m);
     if (op.UK128) return;
-    const long long V = c.V, Mt = (long long)c.M[0] * c.M[1] * c.M[2];
+    const long long V = c.V;
     double2* TK = nullptr;
     double2* UK = nullptr;
     float2* UK64 = nullptr;
@@ -31,11 +31,11 @@ void ensure_curl(Ctx& c) {
         VIE_HIP(hipMalloc(&UK64, 30 * c.Osz * sizeof(float2)));
         AssemblyTables tab = build_curl_tables(c.D, c.k0);
         assemble_blocks(TK, tab, c.N[0], c.N[1], c.N[2], c.stream);
-        double2* circ = static_cast<double2*>(c.ws.get(Mt * sizeof(double2)));
+        const size_t bytes = spectra_scratch_bytes(c.N, c.M);
+        double2* scratch = static_cast<double2*>(c.ws.get(bytes));
         const double2* tws[3] = {c.ax[0].tw128, c.ax[1].tw128, c.ax[2].tw128};
         FftPlan plans[3] = {c.ax[0].plan, c.ax[1].plan, c.ax[2].plan};
-        embed_and_transform(UK, UK64, TK, circ, c.N[0], c.N[1], c.N[2], c.M[0], c.M[1], c.M[2], plans, tws,
-                            c.stream, true);
+        operator_spectra(UK, UK64, TK, scratch, bytes, c.N, c.M, plans, tws, c.stream, true);
         VIE_HIP(hipStreamSynchronize(c.stream));
     } catch (...) {
         if (TK) (void)hipFree(TK);

@@ -3,10 +3,13 @@
 // reflection signs of the PWL bases, forward FFT, octant extraction.
 #include <algorithm>
 #include <cmath>
+#include <mutex>
 #include <vector>
 
 #include "assembly.hpp"
+#include "fft.hpp"
 #include "kernels.hpp"
+#include "vie.h"
 
 namespace vie {
 
@@ -376,8 +379,9 @@ FarTables build_far_tables(const AssemblyTables& T) {
 // contraction for the (ky, kz) pairs in use, and the x accumulation of every
 // (entry, term) sum; the wavefronts' sums are added in order at the end.
 // W = 4 for the near bands, whose 19, 98 and 604 offsets leave most of the
-// chip idle and wait on one wavefront's serial chain (270, 76 and 74 us; 576, 326 and 199 us
-// with W = 1); the far bands have thousands of offsets and take W = 1.
+// chip idle and wait on one wavefront's serial chain (270, 76 and 74 us;
+// with W = 1 576, 326 and 199 us); the far bands have thousands of offsets
+// and take W = 1.
 template <int P, int W>
 __global__ void __launch_bounds__(64 * W) k_assemble_far(double2* __restrict__ out, const FarTables* __restrict__ Fg,
                                                          int b, double Dx, double Dy, double Dz, double k0, int Nx,
@@ -537,45 +541,73 @@ __global__ void __launch_bounds__(kNearThreads) k_assemble_near(double2* __restr
     }
 }
 
-// circulant embedding of one unique entry on the M grid ([Mz][My][Mx]):
-// index j_i -> offset d_i = j_i (j_i < N_i), j_i - M_i (j_i > M_i - N_i),
-// otherwise zero; negative offsets by reflection, T(.., -d_i, ..) =
-// sigma_i(a) sigma_i(b) T(.., d_i, ..)
-__global__ void k_embed(double2* __restrict__ circ, const double2* __restrict__ Te, int Nx, int Ny, int Nz, int Mx,
-                        int My, int Mz, int sgnx, int sgny, int sgnz) {
-    const long long M = (long long)Mx * My * Mz;
-    const long long j = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (j >= M) return;
-    const int jx = int(j % Mx), jy = int((j / Mx) % My), jz = int(j / ((long long)Mx * My));
-    int dx, dy, dz;
-    double s = 1.0;
-    auto map = [](int jj, int N, int MM, int sg, int& d, double& s) {
-        if (jj < N) { d = jj; return true; }
-        if (jj > MM - N) { d = MM - jj; s *= sg; return true; }
-        return false;
-    };
-    double2 val = make_double2(0, 0);
-    if (map(jx, Nx, Mx, sgnx, dx, s) && map(jy, Ny, My, sgny, dy, s) && map(jz, Nz, Mz, sgnz, dz, s)) {
-        double2 t = Te[((long long)dz * Ny + dy) * Nx + dx];
-        val = make_double2(s * t.x, s * t.y);
-    }
-    circ[j] = val;
-}
+// One axis of the operator spectra (Sec. IV-A): every pencil of the N
+// offsets d >= 0 along the axis is extended to the circulant of length M in
+// LDS (index j -> offset j for j < N, M - j with the entry's reflection sign
+// for j > M - N, otherwise zero), transformed, and only its octant half
+// xi <= M / 2 is kept, since C^(M - xi) = sign C^(xi).  With the mirror taken
+// per axis the three passes move 60 V values each way instead of 60 full
+// circulants of 8 V, and the entries of a chunk share one launch: 0.67 ms at
+// 48^3 in 27 launches, against 3.6 ms for the whole circulants in 300.
+//
+// Pencil (e, o, t): element k at in + e in_e + o in_o + k in_k + t; ROWS:
+// the pencils are contiguous rows (t counts rows, in_k = 1) and row t of
+// entry e goes to U[(t nent + e0 + e)][O].  Bound by LDS latency: two ping-pong
+// buffers of `tile` pencils per workgroup, the run-time radix plan.
+struct SpecPass {
+    FftPlan plan;
+    int N, O;              // input offsets, kept outputs
+    int tile, pitch;       // pencils per workgroup, LDS pitch
+    int n_inner;           // extent of t
+    long long in_e, in_o, in_k, out_e, out_o, out_k;
+    unsigned long long neg;   // bit e set: the entry's reflection sign is -1
+    int e0, nent;          // first entry of the chunk, entries in all
+};
+constexpr int kSpecThreads = 128;
 
-// keep the octant xi_i <= M_i / 2 of a transformed circulant, stored as
-// U[oz][oy][e][ox] (the 60 entries of one (oz, oy) row together)
-__global__ void k_octant(double2* __restrict__ U128, float2* __restrict__ U64, const double2* __restrict__ circ,
-                         int e, int nent, int Mx, int My, int Ox, int Oy, int Oz) {
-    const long long O = (long long)Ox * Oy * Oz;
-    const long long o = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (o >= O) return;
-    const int ox = int(o % Ox);
-    const long long row = o / Ox;   // oz * Oy + oy
-    const int oy = int(row % Oy), oz = int(row / Oy);
-    const double2 v = circ[((long long)oz * My + oy) * Mx + ox];
-    const long long dst = (row * nent + e) * Ox + ox;
-    U128[dst] = v;
-    if (U64) U64[dst] = make_float2((float)v.x, (float)v.y);
+template <bool ROWS>
+__global__ void __launch_bounds__(kSpecThreads) k_spectrum_axis(const double2* __restrict__ in,
+                                                                double2* __restrict__ out, float2* __restrict__ out64,
+                                                                SpecPass p, const double2* __restrict__ tw) {
+    extern __shared__ unsigned char smem_raw[];
+    const int M = p.plan.n, tile = p.tile, pitch = p.pitch;
+    double2* buf0 = reinterpret_cast<double2*>(smem_raw);
+    double2* buf1 = buf0 + (ROWS ? tile : M) * pitch;
+    const int tid = threadIdx.x;
+    const int e = blockIdx.z;
+    const long long o = blockIdx.y, t0 = (long long)blockIdx.x * tile;
+    const int nt = (int)min((long long)tile, p.n_inner - t0);
+    const double sg = (p.neg >> (p.e0 + e)) & 1 ? -1.0 : 1.0;
+    const double2* src = in + e * p.in_e + o * p.in_o;
+    for (int idx = tid; idx < M * tile; idx += kSpecThreads) {
+        const int k = ROWS ? idx % M : idx / tile, t = ROWS ? idx / M : idx % tile;
+        double2 v = make_double2(0, 0);
+        if (t < nt && (k < p.N || k > M - p.N)) {
+            const int d = k < p.N ? k : M - k;
+            const double s = k < p.N ? 1.0 : sg;
+            const double2 u = ROWS ? src[(t0 + t) * p.N + d] : src[d * p.in_k + t0 + t];
+            v = make_double2(s * u.x, s * u.y);
+        }
+        buf0[ROWS ? t * pitch + k : k * pitch + t] = v;
+    }
+    __syncthreads();
+    const double2* res = fft_lds<double, true, ROWS>(buf0, buf1, p.plan, tile, ROWS ? pitch : 1, ROWS ? 1 : pitch, tw,
+                                                     tid, kSpecThreads);
+    if (ROWS) {
+        for (int idx = tid; idx < p.O * nt; idx += kSpecThreads) {
+            const int t = idx / p.O, k = idx - t * p.O;
+            const double2 v = res[t * pitch + k];
+            const long long dst = ((t0 + t) * p.nent + p.e0 + e) * p.O + k;
+            out[dst] = v;
+            if (out64) out64[dst] = make_float2((float)v.x, (float)v.y);
+        }
+    } else {
+        double2* dst = out + e * p.out_e + o * p.out_o + t0;
+        for (int idx = tid; idx < p.O * tile; idx += kSpecThreads) {
+            const int k = idx / tile, t = idx - k * tile;
+            if (t < nt) dst[k * p.out_k + t] = res[k * pitch + t];
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -647,46 +679,85 @@ int curl_refl_sign(int e, int axis) {
     return s;
 }
 
-void embed_and_transform(double2* U128, float2* U64, const double2* T, double2* circ, int Nx, int Ny, int Nz,
-                         int Mx, int My, int Mz, const FftPlan plans[3], const double2* const tw[3],
-                         hipStream_t s, bool curl) {
-    const long long V = (long long)Nx * Ny * Nz;
-    const long long M = (long long)Mx * My * Mz;
-    const int Ox = Mx / 2 + 1, Oy = My / 2 + 1, Oz = Mz / 2 + 1;
-    const long long O = (long long)Ox * Oy * Oz;
+// values of scratch one entry needs between its passes: [Oz][Ny][Nx] after
+// z, [Oz][Oy][Nx] after y
+static long long spectrum_values(const int N[3], const int M[3]) {
+    const long long Oz = M[2] / 2 + 1, Oy = M[1] / 2 + 1;
+    return Oz * N[1] * N[0] + Oz * Oy * N[0];
+}
+
+// Scratch of the spectra: chunks of entries go through the three passes
+// together, about 7 in 16 V values (a quarter of what a complex128 product
+// will need), all of them where that is below 8 MiB (small grids, where the
+// launches count), at least one.
+size_t spectra_scratch_bytes(const int N[3], const int M[3]) {
+    const long long per = spectrum_values(N, M), V = (long long)N[0] * N[1] * N[2];
+    const long long most = std::max<long long>(16 * V, (8LL << 20) / (long long)sizeof(double2));
+    return (size_t)std::max(per, std::min(60 * per, most / per * per)) * sizeof(double2);
+}
+
+void operator_spectra(double2* U128, float2* U64, const double2* T, double2* scratch, size_t scratch_bytes,
+                      const int N[3], const int M[3], const FftPlan plans[3], const double2* const tw[3],
+                      hipStream_t s, bool curl) {
+    const long long V = (long long)N[0] * N[1] * N[2], per = spectrum_values(N, M);
+    const int Ox = M[0] / 2 + 1, Oy = M[1] / 2 + 1, Oz = M[2] / 2 + 1;
     const int nent = curl ? 30 : 60;
-    for (int e = 0; e < nent; ++e) {
-        int sg[3];
-        for (int ax = 0; ax < 3; ++ax) sg[ax] = curl ? curl_refl_sign(e, ax) : unique_refl_sign(e, ax);
-        hipLaunchKernelGGL(k_embed, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, circ, T + e * V, Nx, Ny, Nz,
-                           Mx, My, Mz, sg[0], sg[1], sg[2]);
+    const int chunk = (int)std::min<long long>(nent, (long long)(scratch_bytes / sizeof(double2)) / per);
+    VIE_REQUIRE(chunk >= 1, VIE_EINVAL, "operator spectra: scratch below one entry");
+    SpecPass ps[3];
+    for (int ax = 0; ax < 3; ++ax) {
+        SpecPass& p = ps[ax];
+        p = SpecPass{};
+        p.plan = plans[ax];
+        p.N = N[ax];
+        p.O = M[ax] / 2 + 1;
+        p.nent = nent;
+        // up to 8 pencils (whole 128-byte lines) in 64 KiB of LDS, one at the longest lengths
+        p.tile = std::max(1, std::min(8, (int)(64 * 1024 / (2 * sizeof(double2) * M[ax]))));
+        p.pitch = ax == 0 ? M[ax] + 1 : p.tile;
+        for (int e = 0; e < nent; ++e)
+            if ((curl ? curl_refl_sign(e, ax) : unique_refl_sign(e, ax)) < 0) p.neg |= 1ULL << e;
+    }
+    // z: [e][Nz][Ny Nx] -> [e][Oz][Ny Nx]
+    ps[2].n_inner = N[0] * N[1];
+    ps[2].in_e = V;
+    ps[2].in_k = ps[2].out_k = (long long)N[0] * N[1];
+    ps[2].out_e = (long long)Oz * N[1] * N[0];
+    // y: [e][Oz][Ny][Nx] -> [e][Oz][Oy][Nx]
+    ps[1].n_inner = N[0];
+    ps[1].in_e = ps[2].out_e;
+    ps[1].in_o = (long long)N[1] * N[0];
+    ps[1].in_k = ps[1].out_k = N[0];
+    ps[1].out_e = (long long)Oz * Oy * N[0];
+    ps[1].out_o = (long long)Oy * N[0];
+    // x: rows [e][Oz Oy][Nx] -> U[Oz Oy][nent][Ox]
+    ps[0].n_inner = Oz * Oy;
+    ps[0].in_e = ps[1].out_e;
+    auto lds = [](const SpecPass& p, bool rows) {
+        return 2 * (size_t)(rows ? p.tile : p.plan.n) * p.pitch * sizeof(double2);
+    };
+    static std::once_flag once;
+    std::call_once(once, [] {
+        (void)hipFuncSetAttribute((const void*)k_spectrum_axis<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  160 * 1024);
+        (void)hipFuncSetAttribute((const void*)k_spectrum_axis<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  160 * 1024);
+        (void)hipGetLastError();
+    });
+    double2* A = scratch;
+    double2* B = scratch + (long long)chunk * ps[2].out_e;
+    for (int e0 = 0; e0 < nent; e0 += chunk) {
+        const unsigned ne = (unsigned)std::min(chunk, nent - e0);
+        for (auto& p : ps) p.e0 = e0;
+        auto tiles = [](const SpecPass& p) { return (unsigned)((p.n_inner + p.tile - 1) / p.tile); };
+        hipLaunchKernelGGL(k_spectrum_axis<false>, dim3(tiles(ps[2]), 1, ne), dim3(kSpecThreads), lds(ps[2], false), s,
+                           T + e0 * V, A, (float2*)nullptr, ps[2], tw[2]);
         VIE_HIP(hipGetLastError());
-        // z pass: pencils along z, inner x (full length)
-        StridedPass pz{};
-        pz.plan = plans[2];
-        pz.n_in = pz.n_out = Mz;
-        pz.n_inner = Mx;
-        pz.tile = strided_tile_for((int)sizeof(double2), Mz, 16);
-        pz.pitch = pz.tile;
-        pz.in_s1 = pz.out_s1 = 0;
-        pz.in_sc = pz.out_sc = 0;
-        pz.in_s2 = pz.out_s2 = Mx;          // o2 = y
-        pz.in_sk = pz.out_sk = (long long)Mx * My;
-        launch_strided<double>(true, circ, circ, pz, My, 1, tw[2], nullptr, s);
-        StridedPass py{};
-        py.plan = plans[1];
-        py.n_in = py.n_out = My;
-        py.n_inner = Mx;
-        py.tile = strided_tile_for((int)sizeof(double2), My, 16);
-        py.pitch = py.tile;
-        py.in_s1 = py.out_s1 = 0;
-        py.in_sc = py.out_sc = 0;
-        py.in_s2 = py.out_s2 = (long long)Mx * My;   // o2 = z
-        py.in_sk = py.out_sk = Mx;
-        launch_strided<double>(true, circ, circ, py, Mz, 1, tw[1], nullptr, s);
-        launch_rows<double>(true, circ, (long long)My * Mz, plans[0], tw[0], s);
-        hipLaunchKernelGGL(k_octant, dim3((unsigned)((O + 255) / 256)), dim3(256), 0, s, U128, U64, circ, e, nent,
-                           Mx, My, Ox, Oy, Oz);
+        hipLaunchKernelGGL(k_spectrum_axis<false>, dim3(tiles(ps[1]), (unsigned)Oz, ne), dim3(kSpecThreads),
+                           lds(ps[1], false), s, A, B, (float2*)nullptr, ps[1], tw[1]);
+        VIE_HIP(hipGetLastError());
+        hipLaunchKernelGGL(k_spectrum_axis<true>, dim3(tiles(ps[0]), 1, ne), dim3(kSpecThreads), lds(ps[0], true), s,
+                           B, U128, U64, ps[0], tw[0]);
         VIE_HIP(hipGetLastError());
     }
 }

@@ -1234,31 +1234,6 @@ static void launch_p3_ct_n(C<R>* A, const C<R>* U, const P3Params& p, const C<R>
 }
 
 // ---------------------------------------------------------------------------
-// contiguous full-length FFT of rows (operator set-up)
-// ---------------------------------------------------------------------------
-template <typename R, bool FWD>
-__global__ void __launch_bounds__(256) k_rows(C<R>* __restrict__ data, long long nrows, int rows_per_block,
-                                              FftPlan plan, int pitch, const C<R>* __restrict__ tw) {
-    extern __shared__ unsigned char smem_raw[];
-    C<R>* buf0 = reinterpret_cast<C<R>*>(smem_raw);
-    C<R>* buf1 = buf0 + rows_per_block * pitch;
-    const int tid = threadIdx.x, nthr = blockDim.x;
-    const int n = plan.n;
-    const long long r0 = (long long)blockIdx.x * rows_per_block;
-    const int nr = (int)min((long long)rows_per_block, nrows - r0);
-    for (int idx = tid; idx < rows_per_block * n; idx += nthr) {
-        const int rr = idx / n, k = idx - rr * n;
-        buf0[rr * pitch + k] = rr < nr ? data[(r0 + rr) * n + k] : mk<R>(0, 0);
-    }
-    __syncthreads();
-    C<R>* res = fft_lds<R, FWD, true>(buf0, buf1, plan, rows_per_block, pitch, 1, tw, tid, nthr);
-    for (int idx = tid; idx < nr * n; idx += nthr) {
-        const int rr = idx / n, k = idx - rr * n;
-        data[(r0 + rr) * n + k] = res[rr * pitch + k];
-    }
-}
-
-// ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
 template <typename R, bool FWD, bool EPI>
@@ -1392,17 +1367,6 @@ void launch_p3_pwc(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hi
                             "320, 384 or 512");
 }
 
-template <typename R>
-void launch_rows(bool fwd, C<R>* data, long long nrows, const FftPlan& plan, const C<R>* tw, hipStream_t s) {
-    int rpb = std::max(1, std::min(16, 2048 / plan.n));
-    int pitch = plan.n;
-    size_t lds = 2 * (size_t)rpb * pitch * sizeof(C<R>);
-    dim3 grid((unsigned)((nrows + rpb - 1) / rpb));
-    if (fwd) hipLaunchKernelGGL((k_rows<R, true>), grid, dim3(256), lds, s, data, nrows, rpb, plan, pitch, tw);
-    else hipLaunchKernelGGL((k_rows<R, false>), grid, dim3(256), lds, s, data, nrows, rpb, plan, pitch, tw);
-    VIE_HIP(hipGetLastError());
-}
-
 template void launch_strided<float>(bool, const C<float>*, C<float>*, const StridedPass&, long long, long long,
                                     const C<float>*, const Epilogue<float>*, hipStream_t);
 template void launch_strided<double>(bool, const C<double>*, C<double>*, const StridedPass&, long long, long long,
@@ -1411,6 +1375,5 @@ template void launch_p3<float>(C<float>*, const C<float>*, const P3Params&, cons
 template void launch_p3<double>(C<double>*, const C<double>*, const P3Params&, const C<double>*, hipStream_t);
 template void launch_p3_pwc<float>(C<float>*, const C<float>*, const P3Params&, const C<float>*, hipStream_t);
 template void launch_p3_pwc<double>(C<double>*, const C<double>*, const P3Params&, const C<double>*, hipStream_t);
-template void launch_rows<double>(bool, C<double>*, long long, const FftPlan&, const C<double>*, hipStream_t);
 
 }  // namespace vie
