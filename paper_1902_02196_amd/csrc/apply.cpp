@@ -34,6 +34,18 @@ template <> const C<double>* curlspec<double>(const Ctx& c) { return c.op->UK128
 
 static int pick_tile(int n, size_t elem) { return strided_tile_for((int)elem, n, 16); }
 
+// x-pass variant without autotuning: the matrix cores (6) at every length they
+// are compiled for, except where 24 rows leave too few workgroups per CU and
+// the light variant (1), with 12 rows, is level or faster: 256 (complex64
+// 251 us against 272 at 128 x 64 x 64, 897 against 1086 for four vectors;
+// complex128 547 against 563) and 192 in complex128 (449 against 473 at
+// 96 x 64 x 64).  Elsewhere 6 won by 6% (128 complex64) to 4 times (64
+// complex128).  Lengths without either: the staged run-time kernel (0).
+static int p3_default_variant(int es, int n) {
+    if (p3_ct_supported(n) && (n == 256 || (es == 16 && n == 192))) return 1;
+    return p3_mx_fits(es, n) ? 6 : p3_ct_supported(n) ? 1 : 0;
+}
+
 // bytes of FFT intermediates one product of nrhs vectors needs (layouts below)
 size_t apply_workspace_bytes(const Ctx& c, int nrhs, size_t es) {
     const long long row = (long long)c.nc * c.N[0];
@@ -199,13 +211,13 @@ void apply_op(Ctx& c, int op, int nrhs, const C<R>* x, C<R>* y, const C<R>* rhs,
                          2 * g * Mx > nt))
             --g;
         p3.sib_blocks = 1;
-        p3.variant = 0;
-        if (p3_ct_supported(Mx)) {
-            // light variant (one pencil group per workgroup) unless the
-            // autotuner chose the staged one; the staged variant shares the
-            // operator row among all siblings and right-hand sides of a
-            // workgroup
-            p3.variant = tn.p3_variant >= 0 ? tn.p3_variant : 1;
+        p3.variant = tn.p3_variant;
+        if (p3.variant < 0) p3.variant = p3_default_variant((int)es, Mx);
+        if (p3.variant == 6) {
+            g = 1;
+        } else if (p3_ct_supported(Mx)) {
+            // the staged variant shares the operator row among all siblings
+            // and right-hand sides of a workgroup
             if (p3.variant == 0 && !p3_ct_fits((int)es, Mx)) p3.variant = 1;   // staged row would not fit LDS
             p3.sib_blocks = tn.p3_sib_blocks ? tn.p3_sib_blocks : 1;
             g = std::min(p3_ct_groups((int)es, Mx), (4 / p3.sib_blocks) * nrhs);

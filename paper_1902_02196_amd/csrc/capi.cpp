@@ -697,15 +697,17 @@ int vie_set_tuning(vie_ctx* ctx, int precision, int nrhs, const int* choice) {
         t.p3_sib_blocks = choice[1];
         t.tile_z = choice[2];
         t.tile_y = choice[3];
-        VIE_REQUIRE(t.p3_variant >= 0 && t.p3_variant <= 5, VIE_EINVAL, "unknown x-pass variant");
+        VIE_REQUIRE(t.p3_variant >= 0 && t.p3_variant <= 6, VIE_EINVAL, "unknown x-pass variant");
         VIE_REQUIRE(t.p3_variant != 5 || p3_pair_fits(es, c.M[0]), VIE_EINVAL,
                     "the right-hand-side pair variant needs a compiled x length whose 24 rows fit LDS");
         VIE_REQUIRE(t.p3_variant != 0 || !p3_ct_supported(c.M[0]) || p3_ct_fits(es, c.M[0]), VIE_EINVAL,
                     "x-pass variant 0 does not fit LDS for this fft length and precision");
         VIE_REQUIRE(t.p3_variant != 3 || p3_pref_fits(c.M[0]), VIE_EINVAL,
                     "x-pass variant 3 needs an fft length <= 128 along x");
-        VIE_REQUIRE(t.p3_variant == 0 || p3_ct_supported(c.M[0]), VIE_EINVAL,
-                    "x-pass variants 1 to 4 need a compiled fft length along x");
+        VIE_REQUIRE(t.p3_variant == 0 || t.p3_variant == 6 || p3_ct_supported(c.M[0]), VIE_EINVAL,
+                    "x-pass variants 1 to 5 need a compiled fft length along x");
+        VIE_REQUIRE(t.p3_variant != 6 || p3_mx_fits(es, c.M[0]), VIE_EINVAL,
+                    "x-pass variant 6 needs an fft length along x whose rows fit LDS");
         VIE_REQUIRE(t.p3_variant != 2 || p3_quad_fits(es, c.M[0]), VIE_EINVAL,
                     "x-pass variant 2 is complex64 only and needs its rows to fit LDS");
         VIE_REQUIRE(t.p3_sib_blocks == 1 || (t.p3_variant == 0 && (t.p3_sib_blocks == 2 || t.p3_sib_blocks == 4)),

@@ -31,6 +31,15 @@ void launch_strided(bool fwd, const C<R>* in, C<R>* out, const StridedPass& p, l
                     const C<R>* tw, const Epilogue<R>* ep, hipStream_t s);
 template <typename R>
 void launch_p3(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s);
+// the matrix-core x pass (xpass.hpp); false when the length has no kernel
+// whose rows fit LDS
+template <typename R>
+bool launch_p3_mx(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s);
+template <>
+bool launch_p3_mx<float>(C<float>*, const C<float>*, const P3Params&, const C<float>*, hipStream_t);
+template <>
+bool launch_p3_mx<double>(C<double>*, const C<double>*, const P3Params&, const C<double>*, hipStream_t);
+bool p3_mx_fits(int es, int n);
 // x pass of the PWC basis (3 component rows per pencil, compiled lengths only)
 template <typename R>
 void launch_p3_pwc(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s);

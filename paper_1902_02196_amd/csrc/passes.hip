@@ -5,6 +5,7 @@
 #include "kernels.hpp"
 #include "passes.hpp"
 #include "fft_ct.hpp"
+#include "vie.h"
 
 namespace vie {
 
@@ -1276,6 +1277,10 @@ template <typename R>
 void launch_p3(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s) {
     // the compiled kernels skip the zero upper half of each padded row
     VIE_REQUIRE(2 * p.Nx <= p.plan.n, -1, "x pass: fft length below 2 Nx");
+    if (p.variant == 6) {
+        VIE_REQUIRE(launch_p3_mx<R>(A, U, p, tw, s), VIE_EINVAL, "x pass: no matrix-core kernel for this length");
+        return;
+    }
     switch (p.plan.n) {
 #define CASE(n_)                                                                          \
     case n_:                                                                             \

@@ -58,7 +58,7 @@ struct P3Params {
                                // 2: the sibling pencil groups of a row per workgroup (complex64),
                                // 3: as 1 with the operator row prefetched, 4: as 1 with two
                                // threads per frequency, 5: the pencils of two right-hand sides
-                               // per workgroup
+                               // per workgroup, 6: block product on the matrix cores
 };
 
 // workgroup size of the x pass: complex64 1024 threads (128 VGPRs each),

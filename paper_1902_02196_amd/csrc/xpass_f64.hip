@@ -1,0 +1,30 @@
+// Matrix-core x pass, complex128 (xpass.hpp).
+#include "xpass.hpp"
+
+namespace vie {
+
+bool p3_mx_fits(int es, int n) {
+    switch (n) {
+#define CASE(n_) \
+    case n_: return (es == 8 ? p3_mx_lds<float, n_>() : p3_mx_lds<double, n_>()) <= 160 * 1024;
+        VIE_MIX_LENGTHS(CASE)
+#undef CASE
+        default: return false;
+    }
+}
+
+template <>
+bool launch_p3_mx<double>(C<double>* A, const C<double>* U, const P3Params& p, const C<double>* tw, hipStream_t s) {
+    if (!p3_mx_fits(16, p.plan.n) || 2 * p.Nx > p.plan.n) return false;
+    switch (p.plan.n) {
+#define CASE(n_)                                          \
+    case n_:                                             \
+        launch_p3_mx_n<double, n_>(A, U, p, tw, s);   \
+        return true;
+        VIE_MIX_LENGTHS(CASE)
+#undef CASE
+        default: return false;
+    }
+}
+
+}  // namespace vie
