@@ -411,7 +411,8 @@ int vie_autotune(vie_ctx* ctx, int precision, int nrhs, int* choice, double* bes
  * and 320, 384, 512 whose 24 rows fit LDS),
  * workgroups per row (1, 2, 4; variant 0),
  * z tile, y tile (pencils per workgroup of the strided passes: 8 or 16, or
- * 32 where the fft length has a compiled kernel)}.  VIE_EINVAL for shapes
+ * 32 where the fft length has a compiled kernel; lengths with one kernel run
+ * its own tile whichever is named)}.  VIE_EINVAL for shapes
  * this grid cannot run. */
 int vie_set_tuning(vie_ctx* ctx, int precision, int nrhs, const int* choice);
 

@@ -32,7 +32,7 @@ template <typename R> static const C<R>* curlspec(const Ctx& c);
 template <> const C<float>* curlspec<float>(const Ctx& c) { return c.op->UK64; }
 template <> const C<double>* curlspec<double>(const Ctx& c) { return c.op->UK128; }
 
-static int pick_tile(int n, size_t elem) { return strided_tile_for((int)elem, n, 16); }
+static int pick_tile(int n, size_t elem) { return strided_tile_for((int)elem, n); }
 
 // x-pass variant without autotuning: the matrix cores (6) at every length they
 // are compiled for, except where 24 rows leave too few workgroups per CU and

@@ -64,9 +64,21 @@ bool p3_pref_fits(int n);
 template <typename R>
 bool launch_strided_compiled(bool fwd, bool epi, const C<R>* in, C<R>* out, const StridedPass& p, long long n_o2,
                              long long n_o1, const C<R>* tw, const Epilogue<R>& ep, hipStream_t s);
+// strided_mix_*.hip: the fft_mix.hpp lengths, tiles of 128 bytes of pencils
+constexpr int strided_mix_tile(int es) { return 128 / es; }
+template <typename R>
+bool launch_strided_mix(bool fwd, bool epi, const C<R>* in, C<R>* out, const StridedPass& p, long long n_o2,
+                        long long n_o1, const C<R>* tw, const Epilogue<R>& ep, hipStream_t s);
+template <>
+bool launch_strided_mix<float>(bool, bool, const C<float>*, C<float>*, const StridedPass&, long long, long long,
+                               const C<float>*, const Epilogue<float>&, hipStream_t);
+template <>
+bool launch_strided_mix<double>(bool, bool, const C<double>*, C<double>*, const StridedPass&, long long, long long,
+                                const C<double>*, const Epilogue<double>&, hipStream_t);
+bool strided_mix_fits(int es, int n);
 bool strided_ct_fits(int es, int n, int tile);
 bool strided_tile_ok(int es, int n, int tile);
-int strided_tile_for(int es, int n, int preferred);
+int strided_tile_for(int es, int n);
 
 // operator.hip
 AssemblyTables build_assembly_tables(const double D[3], double k0);

@@ -1,6 +1,5 @@
-// Compiled-length strided FFT passes (Sec. IV-A): one kernel per (length,
-// pencils per workgroup, direction, epilogue), kept in their own translation
-// unit.
+// Compiled-length strided FFT passes (Sec. IV-A) that stage their tile in LDS,
+// and the choice between them and the kernels of strided_mix.hpp.
 #include <mutex>
 
 #include "fft_ct.hpp"
@@ -106,25 +105,9 @@ static void launch_strided_ct_nt(const C<R>* in, C<R>* out, const StridedPass& p
     VIE_HIP(hipGetLastError());
 }
 
-template <typename R, bool FWD, bool EPI, int N>
-static void launch_strided_ct_n(const C<R>* in, C<R>* out, const StridedPass& p, long long n_o2, long long n_o1,
-                                const C<R>* tw, const Epilogue<R>& ep, hipStream_t s) {
-    if constexpr (N >= 512) {
-        if (p.tile == 4) {
-            launch_strided_ct_nt<R, FWD, EPI, N, 4>(in, out, p, n_o2, n_o1, tw, ep, s);
-            return;
-        }
-        if (p.tile == 8) {
-            launch_strided_ct_nt<R, FWD, EPI, N, 8>(in, out, p, n_o2, n_o1, tw, ep, s);
-            return;
-        }
-    }
-    if (p.tile == 16) launch_strided_ct_nt<R, FWD, EPI, N, 16>(in, out, p, n_o2, n_o1, tw, ep, s);
-    else launch_strided_ct_nt<R, FWD, EPI, N, 32>(in, out, p, n_o2, n_o1, tw, ep, s);
-}
-
-// compiled strided lengths (tiles of 16 or 32 pencils; also 8 and 4 from 512
-// up, where a larger tile would hold one workgroup per CU)
+// lengths whose tiles of 16 and 32 pencils (also 8 and 4 from 512 up, where a
+// larger tile would hold one workgroup per CU) a caller may ask for; at the
+// lengths of fft_mix.hpp any accepted tile runs that kernel's own
 #define VIE_STRIDED_LENGTHS(X) X(8) X(16) X(32) X(64) X(96) X(128) X(160) X(192) X(256) X(320) X(384) X(512) X(768)
 
 bool strided_ct_fits(int es, int n, int tile) {
@@ -138,37 +121,45 @@ bool strided_ct_fits(int es, int n, int tile) {
     }
 }
 
-// a tile the strided pass can run: 16 or 32 pencils with a compiled length,
-// or 4, 8, 16 pencils in the generic kernel (two buffers within 96 KiB)
+// a tile a caller may ask for: 16 or 32 pencils with a compiled length, or
+// up to 16 pencils whose two buffers in the generic kernel fit 96 KiB, and the
+// tile that strided_tile_for picks
 bool strided_tile_ok(int es, int n, int tile) {
+    if (strided_mix_fits(es, n) && tile == strided_mix_tile(es)) return true;
     if (strided_ct_fits(es, n, tile)) return true;
     return (tile == 1 || tile == 2 || tile == 4 || tile == 8 || tile == 16) && 2LL * tile * n * es <= 96 * 1024;
 }
 
-// pencils per workgroup for a strided pass of length n: `preferred` when the
-// compiled kernel takes it, else 16, else the largest generic tile whose two
-// LDS buffers fit 96 KiB
-int strided_tile_for(int es, int n, int preferred) {
-    if (strided_ct_fits(es, n, preferred)) return preferred;
-    if (strided_ct_fits(es, n, 16)) return 16;
+// pencils per workgroup for a strided pass of length n: the fft_mix.hpp
+// kernel's own, 4 at 768 (32 x 32 x 384 x 2: 86 and 100 us against 136 and
+// 161 with 16), else the largest generic tile whose two LDS buffers fit 96 KiB
+int strided_tile_for(int es, int n) {
+    if (strided_mix_fits(es, n)) return strided_mix_tile(es);
+    if (n == 768) return 4;
     int t = 16;
     while (t > 1 && 2LL * t * n * es > 96 * 1024) t /= 2;
     return t;
 }
 
+// Which kernel runs: the fft_mix.hpp lengths have theirs (strided_mix.hpp),
+// faster than this file's at every size but one, the epilogue pass at 160 and
+// 192 in complex64 (80^3 x 2: 66 us here against 85, 96^3: 61 against 77).
+// 768 is this file's alone.
 template <typename R, bool FWD, bool EPI>
 static bool launch_strided_ct(const C<R>* in, C<R>* out, const StridedPass& p, long long n_o2, long long n_o1,
                               const C<R>* tw, const Epilogue<R>& ep, hipStream_t s) {
-    if (!strided_ct_fits((int)sizeof(C<R>), p.plan.n, p.tile)) return false;
-    switch (p.plan.n) {
-#define CASE(n_)                                                                   \
-    case n_:                                                                      \
-        launch_strided_ct_n<R, FWD, EPI, n_>(in, out, p, n_o2, n_o1, tw, ep, s); \
-        return true;
-        VIE_STRIDED_LENGTHS(CASE)
-#undef CASE
-        default: return false;
+    if constexpr (EPI && sizeof(R) == 4) {
+        if (p.plan.n == 160) launch_strided_ct_nt<R, FWD, EPI, 160, 16>(in, out, p, n_o2, n_o1, tw, ep, s);
+        if (p.plan.n == 192) launch_strided_ct_nt<R, FWD, EPI, 192, 16>(in, out, p, n_o2, n_o1, tw, ep, s);
+        if (p.plan.n == 160 || p.plan.n == 192) return true;
     }
+    if (p.plan.n != 768) return launch_strided_mix<R>(FWD, EPI, in, out, p, n_o2, n_o1, tw, ep, s);
+    if (!strided_ct_fits((int)sizeof(C<R>), 768, p.tile)) return false;
+    if (p.tile == 4) launch_strided_ct_nt<R, FWD, EPI, 768, 4>(in, out, p, n_o2, n_o1, tw, ep, s);
+    else if (p.tile == 8) launch_strided_ct_nt<R, FWD, EPI, 768, 8>(in, out, p, n_o2, n_o1, tw, ep, s);
+    else if (p.tile == 16) launch_strided_ct_nt<R, FWD, EPI, 768, 16>(in, out, p, n_o2, n_o1, tw, ep, s);
+    else launch_strided_ct_nt<R, FWD, EPI, 768, 32>(in, out, p, n_o2, n_o1, tw, ep, s);
+    return true;
 }
 
 template <typename R>

@@ -48,6 +48,11 @@ static double time_apply(Ctx& c, int nrhs, const C<R>* x, C<R>* y) {
     return best;
 }
 
+// lengths with one strided kernel have one tile to try
+static bool tile_candidate(int es, int n, int tile) {
+    return strided_mix_fits(es, n) ? tile == strided_mix_tile(es) : strided_tile_ok(es, n, tile);
+}
+
 template <typename R>
 static Tune tune_t(Ctx& c, int nrhs, double* best_ms) {
     const size_t n = (size_t)c.nc * c.V * nrhs;
@@ -74,7 +79,7 @@ static Tune tune_t(Ctx& c, int nrhs, double* best_ms) {
                     t.p3_sib_blocks = sb;
                     t.tile_z = tz;
                     t.tile_y = ty;
-                    if (!strided_tile_ok((int)sizeof(C<R>), c.M[2], tz) || !strided_tile_ok((int)sizeof(C<R>), c.M[1], ty))
+                    if (!tile_candidate((int)sizeof(C<R>), c.M[2], tz) || !tile_candidate((int)sizeof(C<R>), c.M[1], ty))
                         continue;
                     cands.push_back(t);
                 }
