@@ -72,14 +72,22 @@ template <typename R, int N, int T> constexpr size_t mix_lds() {
     return MixShape<N, 0>::LAST ? 0 : (size_t)N * mix_pitch<T>() * sizeof(C<R>);
 }
 
-template <typename R, bool FWD, int N, int T, int NT, int S, typename Load, typename Store>
+template <typename R, bool FWD, int N, int T, int NT, int S, typename Load, typename Pre, typename Store>
 __device__ __forceinline__ void mix_passes(C<R>* buf, const C<R>* __restrict__ tw, int tid, Load load,
-                                           Store store) {
+                                           Pre pre, Store store) {
     using P = MixShape<N, S>;
     constexpr int RAD = P::RAD, NS = P::NS, nb = N / RAD, TP = mix_pitch<T>();
     constexpr int WORK = nb * T, ROUNDS = (WORK + NT - 1) / NT;
     constexpr bool FIRST = S == 0, LAST = P::LAST, MIDDLE = !FIRST && !LAST;
     C<R> v[MIDDLE ? ROUNDS : 1][RAD];
+    decltype(pre(0, 0)) ex[LAST ? RAD : 1];   // what the outputs will be combined with
+    auto prefetch = [&](int q) {
+        const int w = tid + q * NT, j = w / T, t = w - j * T, k = j % NS, c0 = (j - k) * RAD + k;
+        if (WORK % NT != 0 && w >= WORK) return;
+#pragma unroll
+        for (int i = 0; i < RAD; ++i)
+            if (FWD || 2 * i * NS < N) ex[i] = pre(c0 + i * NS, t);
+    };
     auto butterfly = [&](int q, C<R>* v) {
         const int w = tid + q * NT, j = w / T, t = w - j * T, k = j % NS;
         if (WORK % NT != 0 && w >= WORK) return;
@@ -106,7 +114,7 @@ __device__ __forceinline__ void mix_passes(C<R>* buf, const C<R>* __restrict__ t
         if constexpr (LAST) {
 #pragma unroll
             for (int i = 0; i < RAD; ++i)
-                if (FWD || 2 * i * NS < N) store(c0 + i * NS, t, v[i]);   // beyond: cropped
+                if (FWD || 2 * i * NS < N) store(c0 + i * NS, t, v[i], ex[i]);   // beyond: cropped
         } else {
 #pragma unroll
             for (int i = 0; i < RAD; ++i) buf[(c0 + i * NS) * TP + t] = v[i];
@@ -121,13 +129,14 @@ __device__ __forceinline__ void mix_passes(C<R>* buf, const C<R>* __restrict__ t
     } else {
 #pragma unroll
         for (int q = 0; q < ROUNDS; ++q) {
+            if constexpr (LAST) prefetch(q);
             butterfly(q, v[0]);
             put(q, v[0]);
         }
     }
     if constexpr (!LAST) {
         __syncthreads();
-        mix_passes<R, FWD, N, T, NT, S + 1>(buf, tw, tid, load, store);
+        mix_passes<R, FWD, N, T, NT, S + 1>(buf, tw, tid, load, pre, store);
     }
 }
 
@@ -152,24 +161,35 @@ __global__ void __launch_bounds__(mix_threads(N, T)) k_strided_mix(const C<R>* i
     auto load = [&](int k, int t) {
         return k < n_in && t < tw_n ? stream_load(&src[k * p.in_sk + t]) : mk<R>(0, 0);   // last read of the input
     };
-    auto store = [&](int k, int t, C<R> w) {
+    // the epilogue's operands are fetched ahead of the last pass, so that their
+    // latency runs beside its LDS reads and butterflies
+    struct Operands { C<R> b, a, x; };
+    const bool has_a = EPI && (ep.a || ep.a_const != R(0));
+    auto pre = [&](int k, int t) {
+        Operands o{};
+        if (EPI && k < n_out && t < tw_n) {
+            const long long v = o2 * p.out_s2 + k * p.out_sk + t0 + t;   // voxel
+            o.b = ep.b ? ep.b[v] : mk<R>(ep.b_const, 0);
+            if (has_a) {
+                o.a = ep.a ? ep.a[v] : mk<R>(ep.a_const, 0);
+                o.x = ep.x[obase + v];
+            }
+        }
+        return o;
+    };
+    auto store = [&](int k, int t, C<R> w, const Operands& o) {
         if (k < n_out && t < tw_n) {
             if (EPI) {
-                const long long v = o2 * p.out_s2 + k * p.out_sk + t0 + t;   // voxel
-                const long long e = obase + v;                                  // element
-                C<R> bv = ep.b ? ep.b[v] : mk<R>(ep.b_const, 0);
-                C<R> y = cscale(cmul(bv, w), ep.gb[l]);
-                if (ep.a || ep.a_const != R(0)) {
-                    C<R> av = ep.a ? ep.a[v] : mk<R>(ep.a_const, 0);
-                    y = cadd(y, cscale(cmul(av, ep.x[e]), ep.ga[l]));
-                }
+                const long long e = obase + o2 * p.out_s2 + k * p.out_sk + t0 + t;   // element
+                C<R> y = cscale(cmul(o.b, w), ep.gb[l]);
+                if (has_a) y = cadd(y, cscale(cmul(o.a, o.x), ep.ga[l]));
                 if (ep.rhs) y = cadd(y, ep.rhs[e]);
                 w = y;
             }
             dst[k * p.out_sk + t] = w;
         }
     };
-    mix_passes<R, FWD, N, T, NT, 0>(buf, tw, threadIdx.x, load, store);
+    mix_passes<R, FWD, N, T, NT, 0>(buf, tw, threadIdx.x, load, pre, store);
 }
 
 template <typename R, bool FWD, bool EPI, int N, int T>
