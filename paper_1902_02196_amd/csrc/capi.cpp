@@ -62,13 +62,12 @@ void Ctx::free_mcontrast() {
 
 }  // namespace vie
 
-// octant spectra of the context's 60 tensors, through the FFT workspace
+// octant spectra of the context's 60 tensors
 static void build_spectra(Ctx& c) {
-    const size_t bytes = spectra_scratch_bytes(c.N, c.M);
-    double2* scratch = static_cast<double2*>(c.ws.get(bytes));
+    const SpectraScratch scratch(c);
     const double2* tws[3] = {c.ax[0].tw128, c.ax[1].tw128, c.ax[2].tw128};
     const FftPlan plans[3] = {c.ax[0].plan, c.ax[1].plan, c.ax[2].plan};
-    operator_spectra(c.U128, c.U64, c.T, scratch, bytes, c.N, c.M, plans, tws, c.stream);
+    operator_spectra(c.U128, c.U64, c.T, scratch.p, scratch.bytes, c.N, c.M, plans, tws, c.stream);
 }
 
 static void check_ctx(vie_ctx* ctx) { VIE_REQUIRE(ctx != nullptr, VIE_EINVAL, "null context"); }

@@ -31,11 +31,10 @@ void ensure_curl(Ctx& c) {
         VIE_HIP(hipMalloc(&UK64, 30 * c.Osz * sizeof(float2)));
         AssemblyTables tab = build_curl_tables(c.D, c.k0);
         assemble_blocks(TK, tab, c.N[0], c.N[1], c.N[2], c.stream);
-        const size_t bytes = spectra_scratch_bytes(c.N, c.M);
-        double2* scratch = static_cast<double2*>(c.ws.get(bytes));
+        const SpectraScratch scratch(c);
         const double2* tws[3] = {c.ax[0].tw128, c.ax[1].tw128, c.ax[2].tw128};
         FftPlan plans[3] = {c.ax[0].plan, c.ax[1].plan, c.ax[2].plan};
-        operator_spectra(UK, UK64, TK, scratch, bytes, c.N, c.M, plans, tws, c.stream, true);
+        operator_spectra(UK, UK64, TK, scratch.p, scratch.bytes, c.N, c.M, plans, tws, c.stream, true);
         VIE_HIP(hipStreamSynchronize(c.stream));
     } catch (...) {
         if (TK) (void)hipFree(TK);
