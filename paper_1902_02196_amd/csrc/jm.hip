@@ -137,9 +137,8 @@ void apply_jm(Ctx& c, int op, int nrhs, const C<R>* x, C<R>* y, const C<R>* rhs,
 
 bool jm_fused_supported(const Ctx& c, size_t es) {
     const int Mx = c.M[0];
-    if (!p3_ct_supported(Mx) || 2 * c.N[0] > Mx) return false;
-    if (es == sizeof(C<double>) && Mx > 128) return false;
-    return ((size_t)Mx + (size_t)lds_pad(24 * Mx) + 2) * es <= 160 * 1024;
+    if (2 * c.N[0] > Mx) return false;
+    return p3_jm_supported((int)es, Mx);
 }
 
 template void apply_jm<float>(Ctx&, int, int, const C<float>*, C<float>*, const C<float>*, void*, size_t);

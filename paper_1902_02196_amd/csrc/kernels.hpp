@@ -40,6 +40,24 @@ bool launch_p3_mx<float>(C<float>*, const C<float>*, const P3Params&, const C<fl
 template <>
 bool launch_p3_mx<double>(C<double>*, const C<double>*, const P3Params&, const C<double>*, hipStream_t);
 bool p3_mx_fits(int es, int n);
+// the same for the curl operator (U the 30 tensors) and for the J-M sums
+template <typename R>
+bool launch_p3_mx_curl(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s);
+template <>
+bool launch_p3_mx_curl<float>(C<float>*, const C<float>*, const P3Params&, const C<float>*, hipStream_t);
+template <>
+bool launch_p3_mx_curl<double>(C<double>*, const C<double>*, const P3Params&, const C<double>*, hipStream_t);
+template <typename R>
+bool launch_p3_mx_jm(C<R>* A, const C<R>* UN, const C<R>* UK, const P3Params& p, const C<R>* tw, C<R> kj, C<R> km,
+                     hipStream_t s);
+template <>
+bool launch_p3_mx_jm<float>(C<float>*, const C<float>*, const C<float>*, const P3Params&, const C<float>*, C<float>,
+                            C<float>, hipStream_t);
+template <>
+bool launch_p3_mx_jm<double>(C<double>*, const C<double>*, const C<double>*, const P3Params&, const C<double>*,
+                             C<double>, C<double>, hipStream_t);
+bool p3_mx_jm_fits(int es, int n);
+bool p3_jm_supported(int es, int n);   // either J-M x pass
 // x pass of the PWC basis (3 component rows per pencil, compiled lengths only)
 template <typename R>
 void launch_p3_pwc(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s);

@@ -983,16 +983,12 @@ __global__ void __launch_bounds__(kP3JmThreads) k_p3_jm(C<R>* __restrict__ A, co
     lds_to_rows<R, N, NT>(buf, 24, p.Nx, rowp);
 }
 
-// compiled for complex64 at every length of the list, for complex128 up to
-// 128 (beyond, its 24 rows of butterflies would not stay in registers)
+// the lengths where this kernel is faster than the matrix-core one, or the
+// only one (xpass_jm.hip states the times)
 template <typename R, int N>
 static bool launch_p3_jm_n(C<R>* A, const C<R>* UN, const C<R>* UK, const P3Params& p, const C<R>* tw, C<R> kj,
                            C<R> km, hipStream_t s) {
-    if constexpr (sizeof(R) == 8 && N > 128) {
-        return false;
-    } else {
     const size_t lds = ((size_t)N + lds_pad(24 * N) + 2) * sizeof(C<R>);
-    if (lds > 160 * 1024) return false;
     const long long rows8 = ((long long)p.Oy * p.Oz + 7) / 8 * 8;
     const long long nblk = rows8 * 4LL * p.nrhs;
     VIE_REQUIRE(nblk < (1LL << 31), -1, "J-M x pass: too many workgroups");
@@ -1005,7 +1001,11 @@ static bool launch_p3_jm_n(C<R>* A, const C<R>* UN, const C<R>* UK, const P3Para
                  km);
     VIE_HIP(hipGetLastError());
     return true;
-    }
+}
+
+bool p3_jm_supported(int es, int n) {
+    if (p3_mx_jm_fits(es, n)) return true;
+    return es == 8 ? n == 128 || n == 160 || n == 192 || n == 256 || n == 320 || n == 384 || n == 512 : n == 128;
 }
 
 // x pass of the PWC basis (3 unknowns per voxel, the pulse functions): one
@@ -1311,9 +1311,9 @@ void launch_p3(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStr
     VIE_HIP(hipGetLastError());
 }
 
-// x pass of the curl operator (the staged kernel for any length whose rows
-// fit): the magnetic field's product, and the coupling blocks of the J-M
-// product in both precisions
+// x pass of the curl operator (the matrix-core kernel, or the staged one at
+// the lengths without: 2, 4 and 6): the magnetic field's product, and the
+// coupling blocks of the J-M product in both precisions
 template <typename R>
 void launch_p3_curl(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s) {
     const int nt = p3_threads<R>();
@@ -1321,6 +1321,7 @@ void launch_p3_curl(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, h
                 "magnetic product: fft length along x above 256");
     const size_t lds = (30 * (size_t)p.Ox + lds_pad(p.groups * 12 * p.pitch) + 2) * sizeof(C<R>);
     VIE_REQUIRE(lds <= 150 * 1024, -1, "magnetic product: x rows do not fit LDS");
+    if (launch_p3_mx_curl<R>(A, U, p, tw, s)) return;
     const bool split4 = 4 * p.groups * p.plan.n <= nt;
     static std::once_flag once;
     std::call_once(once, [] {
@@ -1341,12 +1342,15 @@ template <typename R>
 bool launch_p3_jm(C<R>* A, const C<R>* UN, const C<R>* UK, const P3Params& p, const C<R>* tw, C<R> kj, C<R> km,
                   hipStream_t s) {
     if (2 * p.Nx > p.plan.n) return false;
-    switch (p.plan.n) {
-#define CASE(n_)                                                       \
-    case n_:                                                          \
-        return launch_p3_jm_n<R, n_>(A, UN, UK, p, tw, kj, km, s);
-        VIE_P3_LENGTHS(CASE)
-#undef CASE
+    if (launch_p3_mx_jm<R>(A, UN, UK, p, tw, kj, km, s)) return true;
+    if (p.plan.n == 128) return launch_p3_jm_n<R, 128>(A, UN, UK, p, tw, kj, km, s);
+    if constexpr (sizeof(R) == 4) switch (p.plan.n) {
+        case 160: return launch_p3_jm_n<R, 160>(A, UN, UK, p, tw, kj, km, s);
+        case 192: return launch_p3_jm_n<R, 192>(A, UN, UK, p, tw, kj, km, s);
+        case 256: return launch_p3_jm_n<R, 256>(A, UN, UK, p, tw, kj, km, s);
+        case 320: return launch_p3_jm_n<R, 320>(A, UN, UK, p, tw, kj, km, s);
+        case 384: return launch_p3_jm_n<R, 384>(A, UN, UK, p, tw, kj, km, s);
+        case 512: return launch_p3_jm_n<R, 512>(A, UN, UK, p, tw, kj, km, s);
         default: break;
     }
     return false;

@@ -41,6 +41,14 @@
 // complex128 16^3 19.8 -> 9.2, 32^3 92 -> 25, 64^3 294 -> 210; the lengths
 // that had only the run-time kernel 72 x 61 x 85 with three vectors 2593 ->
 // 601, complex128 45 x 50 x 37 with two 710 -> 107.
+//
+// The curl operator K takes the same tiles: 30 tensors instead of 60, one
+// field component of the input fewer per output component.  Complex128 64^3,
+// two vectors, the whole magnetic-field product: 3059 -> 1648 us with the
+// strided passes (the staged kernel before it held a workgroup per CU and ran
+// its length's plan).  The J-M pass holds both coefficient sets of a row (48
+// rows) and applies N and K to each in one visit; p3_mx_jm_fits states where
+// it runs.
 #pragma once
 
 #include <mutex>
@@ -238,72 +246,127 @@ __device__ __forceinline__ void row_passes(C<R>* buf, const Twiddles<R, N>& tw, 
 // value enters with the opposite sign
 constexpr unsigned kFoldX = fold_mask(1, 0, 0), kFoldY = fold_mask(0, 1, 0), kFoldZ = fold_mask(0, 0, 1);
 
-// Block product of one tile of octant frequencies, complex64: 16 frequencies
-// (block b = lane / 4), row or column lane % 4.  Column (fx, sy) reads and
-// writes its own column xi of its own sibling's rows.
-template <int N>
-struct TileN32 {
-    using L = RowLayout<float, N>;
-    static constexpr int TILE = 16, OX = N / 2 + 1, TILES = (OX + TILE - 1) / TILE;
-    float2 a[4][6];   // operator column l', dyad pq, row lane % 4
+// curl operator K^{(p,l),(q,l')} = levi(p, k, q) Q_k^{ll'} (zero for p = q):
+// dyad index and sign of the block (p, q)
+constexpr int curl_k(int p, int q) { return 3 - p - q; }
+constexpr bool curl_neg(int p, int q) { return levi(p, 3 - p - q, q) < 0; }
 
-    __device__ __forceinline__ void load(const float2* __restrict__ U, int tile, int lane) {
-        const int ox = min(tile * TILE + (lane >> 2), OX - 1), i = lane & 3;
-#pragma unroll
-        for (int lp = 0; lp < 4; ++lp) {
+// One tile of octant frequencies in complex64: 16 frequencies (block b =
+// lane / 4), row or column lane % 4.  Column (fx, sy) reads and writes its
+// own column xi of its own sibling's rows.
+template <int N>
+struct Tile32 {
+    using L = RowLayout<float, N>;
+    static constexpr int COUNT = 16, OX = N / 2 + 1, TILES = (OX + COUNT - 1) / COUNT;
+    // operator values of ND dyads: column l', dyad, row lane % 4
+    template <int ND> struct Op {
+        float2 a[4][ND];
+        __device__ __forceinline__ void load(const float2* __restrict__ U, int tile, int lane, int lp) {
+            const int ox = min(tile * COUNT + (lane >> 2), OX - 1), i = lane & 3;
             const int lo = min(i, lp), hi = max(i, lp);
             const int off = (lo * (9 - lo) / 2 + (hi - lo)) * OX + ox;   // ll_index(i + 1, lp + 1)
 #pragma unroll
-            for (int pq = 0; pq < 6; ++pq) a[lp][pq] = U[10 * pq * OX + off];
+            for (int d = 0; d < ND; ++d) a[lp][d] = U[10 * d * OX + off];
         }
-    }
+        __device__ __forceinline__ void load(const float2* __restrict__ U, int tile, int lane) {
+#pragma unroll
+            for (int lp = 0; lp < 4; ++lp) load(U, tile, lane, lp);
+        }
+        // exchanged pulse / linear pairs: column l' = 1, rows l > 1
+        __device__ __forceinline__ void fix(int lane) {
+            const unsigned sa = (lane & 3) ? 0x80000000u : 0u;
+#pragma unroll
+            for (int d = 0; d < ND; ++d) a[0][d] = flip_sign(a[0][d], sa);
+        }
+    };
+    struct Acc { mfma_f4 r[3], i[3]; };
 
-    __device__ __forceinline__ void apply(float2* buf, int tile, int lane, int ny_sib) {
-        const int ox = tile * TILE + (lane >> 2), fx = (lane >> 1) & 1, sy = lane & 1;
+    bool ok;
+    int off;       // of the column in the rows of a pair of siblings
+    unsigned sx;   // x fold
+
+    __device__ __forceinline__ Tile32(int tile, int lane, int ny_sib) {
+        const int ox = tile * COUNT + (lane >> 2), fx = (lane >> 1) & 1, sy = lane & 1;
         // the folded column exists strictly between 0 and N / 2
-        const bool ok = ox < OX && (!fx || (ox > 0 && 2 * ox < N)) && sy < ny_sib;
-        const int oxc = ok ? ox : 0, xi = fx && ok ? N - oxc : oxc;
-        float2* col = buf + (sy && ok ? L::row(12) : 0) + L::col(xi);
-        const unsigned sx = (unsigned)fx << 31;
-        const unsigned sa = (lane & 3) ? 0x80000000u : 0u;   // exchanged pulse / linear pairs: column l' = 1, rows l > 1
-        mfma_f4 yr[3], ym[3];
+        ok = ox < OX && (!fx || (ox > 0 && 2 * ox < N)) && sy < ny_sib;
+        const int oxc = ok ? ox : 0;
+        off = (sy && ok ? L::row(12) : 0) + L::col(fx && ok ? N - oxc : oxc);
+        sx = (unsigned)fx << 31;
+    }
+    static __device__ __forceinline__ void clear(Acc& y) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p) yr[p] = ym[p] = mfma_f4{0, 0, 0, 0};
+        for (int p = 0; p < 3; ++p) y.r[p] = y.i[p] = mfma_f4{0, 0, 0, 0};
+    }
+    // y *= f
+    static __device__ __forceinline__ void scale(Acc& y, float2 f) {
 #pragma unroll
-        for (int lp = 0; lp < 4; ++lp) {
-            float2 x[3];
-            float nx[3];
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float2 v = cmul(make_float2(y.r[p][i], y.i[p][i]), f);
+                y.r[p][i] = v.x;
+                y.i[p][i] = v.y;
+            }
+    }
+    // y += the part of N x or K x from the inputs of scalar basis l' = lp + 1,
+    // x the column of rows at buf
+    template <bool CURL, int ND>
+    __device__ __forceinline__ void accumulate(Acc& y, const Op<ND>& op, const float2* buf, int lp) const {
+        const float2* col = buf + off;
+        float2 x[3], nx[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            x[q] = col[(4 * q + lp) * L::RB];
+            if ((kFoldX >> (4 * q + lp)) & 1) x[q] = flip_sign(x[q], sx);
+            nx[q] = make_float2(-x[q].x, -x[q].y);
+        }
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
-                x[q] = col[(4 * q + lp) * L::RB];
-                if ((kFoldX >> (4 * q + lp)) & 1) x[q] = flip_sign(x[q], sx);
-                nx[q] = -x[q].y;
+                if (CURL && p == q) continue;
+                const float2 v = op.a[lp][CURL ? curl_k(p, q) : pq_index(p, q)];
+                const bool neg = CURL && curl_neg(p, q);
+                const float2 u = neg ? nx[q] : x[q], w = neg ? x[q] : nx[q];
+                y.r[p] = __builtin_amdgcn_mfma_f32_4x4x1f32(v.x, u.x, y.r[p], 0, 0, 0);
+                y.i[p] = __builtin_amdgcn_mfma_f32_4x4x1f32(v.x, u.y, y.i[p], 0, 0, 0);
+                y.r[p] = __builtin_amdgcn_mfma_f32_4x4x1f32(v.y, w.y, y.r[p], 0, 0, 0);
+                y.i[p] = __builtin_amdgcn_mfma_f32_4x4x1f32(v.y, u.x, y.i[p], 0, 0, 0);
             }
-            if (lp == 0) {
+    }
+    template <bool CURL, int ND>
+    __device__ __forceinline__ void accumulate(Acc& y, const Op<ND>& op, const float2* buf) const {
 #pragma unroll
-                for (int pq = 0; pq < 6; ++pq) a[lp][pq] = flip_sign(a[lp][pq], sa);
+        for (int lp = 0; lp < 4; ++lp) accumulate<CURL>(y, op, buf, lp);
+    }
+    // y0 += N x0 and y1 += N x1 (or K), the operator fetched column by column:
+    // with all of it in registers the two sums would spill
+    template <bool CURL, int ND>
+    __device__ __forceinline__ void accumulate2(Acc& y0, Acc& y1, const float2* __restrict__ U, int tile, int lane,
+                                                const float2* x0, const float2* x1) const {
+        Op<ND> op;
+#pragma unroll
+        for (int lp = 0; lp < 4; ++lp) {
+            if (lp % 2 == 0) __builtin_amdgcn_sched_barrier(0);   // loads of two columns in flight
+            op.load(U, tile, lane, lp);
+            if (lp == 0) op.fix(lane);
+            accumulate<CURL>(y0, op, x0, lp);
+            accumulate<CURL>(y1, op, x1, lp);
+        }
+    }
+    // ODD: the operator itself changes sign under the x fold (the curl)
+    template <bool ODD>
+    __device__ __forceinline__ void store(const Acc& y, float2* buf) const {
+        if (!ok) return;
+        float2* col = buf + off;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float2 v = make_float2(y.r[p][i], y.i[p][i]);
+                if ((((kFoldX >> (4 * p + i)) & 1) != 0) != ODD) v = flip_sign(v, sx);
+                col[(4 * p + i) * L::RB] = v;
             }
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    const float2 v = a[lp][pq_index(p, q)];
-                    yr[p] = __builtin_amdgcn_mfma_f32_4x4x1f32(v.x, x[q].x, yr[p], 0, 0, 0);
-                    ym[p] = __builtin_amdgcn_mfma_f32_4x4x1f32(v.x, x[q].y, ym[p], 0, 0, 0);
-                    yr[p] = __builtin_amdgcn_mfma_f32_4x4x1f32(v.y, nx[q], yr[p], 0, 0, 0);
-                    ym[p] = __builtin_amdgcn_mfma_f32_4x4x1f32(v.y, x[q].x, ym[p], 0, 0, 0);
-                }
-        }
-        if (ok) {
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float2 y = make_float2(yr[p][i], ym[p][i]);
-                    if ((kFoldX >> (4 * p + i)) & 1) y = flip_sign(y, sx);
-                    col[(4 * p + i) * L::RB] = y;
-                }
-        }
     }
 };
 
@@ -311,132 +374,199 @@ struct TileN32 {
 // lane % 4, the four l' of an input component at lane / 16; the output row of
 // a column sits at lane / 16.
 template <int N>
-struct TileN64 {
+struct Tile64 {
     using L = RowLayout<double, N>;
-    static constexpr int TILE = 4, OX = N / 2 + 1, TILES = (OX + TILE - 1) / TILE;
-    double2 a[6];
-
-    __device__ __forceinline__ void load(const double2* __restrict__ U, int tile, int lane) {
-        const int ox = min(tile * TILE + ((lane >> 2) & 3), OX - 1), i = lane & 3, lp = lane >> 4;
-        const int lo = min(i, lp), hi = max(i, lp);
-        const int off = (lo * (9 - lo) / 2 + (hi - lo)) * OX + ox;   // ll_index(i + 1, lp + 1)
+    static constexpr int COUNT = 4, OX = N / 2 + 1, TILES = (OX + COUNT - 1) / COUNT;
+    template <int ND> struct Op {
+        double2 a[ND];
+        __device__ __forceinline__ void load(const double2* __restrict__ U, int tile, int lane) {
+            const int ox = min(tile * COUNT + ((lane >> 2) & 3), OX - 1), i = lane & 3, lp = lane >> 4;
+            const int lo = min(i, lp), hi = max(i, lp);
+            const int off = (lo * (9 - lo) / 2 + (hi - lo)) * OX + ox;   // ll_index(i + 1, lp + 1)
 #pragma unroll
-        for (int pq = 0; pq < 6; ++pq) a[pq] = U[10 * pq * OX + off];
-    }
+            for (int d = 0; d < ND; ++d) a[d] = U[10 * d * OX + off];
+        }
+        __device__ __forceinline__ void fix(int lane) {   // exchanged pulse / linear pairs
+            const unsigned sa = lane < 16 && (lane & 3) ? 0x80000000u : 0u;
+#pragma unroll
+            for (int d = 0; d < ND; ++d) a[d] = flip_sign(a[d], sa);
+        }
+    };
+    struct Acc { double r[3], i[3]; };
 
-    __device__ __forceinline__ void apply(double2* buf, int tile, int lane, int ny_sib) {
-        const int ox = tile * TILE + ((lane >> 2) & 3), fx = (lane >> 1) & 1, sy = lane & 1, l = lane >> 4;
-        const bool ok = ox < OX && (!fx || (ox > 0 && 2 * ox < N)) && sy < ny_sib;
-        const int oxc = ok ? ox : 0, xi = fx && ok ? N - oxc : oxc;
-        double2* col = buf + (sy && ok ? L::row(12) : 0) + L::col(xi) + l * L::RB;
-        const unsigned sa = l == 0 && (lane & 3) ? 0x80000000u : 0u;   // exchanged pulse / linear pairs
-        double2 x[3];
-        double nx[3];
+    bool ok;
+    int off, l;
+    unsigned sx;
+
+    __device__ __forceinline__ Tile64(int tile, int lane, int ny_sib) {
+        const int ox = tile * COUNT + ((lane >> 2) & 3), fx = (lane >> 1) & 1, sy = lane & 1;
+        l = lane >> 4;
+        ok = ox < OX && (!fx || (ox > 0 && 2 * ox < N)) && sy < ny_sib;
+        const int oxc = ok ? ox : 0;
+        off = (sy && ok ? L::row(12) : 0) + L::col(fx && ok ? N - oxc : oxc) + l * L::RB;
+        sx = (unsigned)fx << 31;
+    }
+    static __device__ __forceinline__ void clear(Acc& y) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) y.r[p] = y.i[p] = 0;
+    }
+    static __device__ __forceinline__ void scale(Acc& y, double2 f) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const double2 v = cmul(make_double2(y.r[p], y.i[p]), f);
+            y.r[p] = v.x;
+            y.i[p] = v.y;
+        }
+    }
+    template <bool CURL, int ND>
+    __device__ __forceinline__ void accumulate(Acc& y, const Op<ND>& op, const double2* buf) const {
+        const double2* col = buf + off;
+        double2 x[3], nx[3];
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            const unsigned sx = fx ? ((kFoldX >> (4 * q + l)) & 1) << 31 : 0u;
-            x[q] = flip_sign(col[4 * q * L::RB], sx);
-            nx[q] = -x[q].y;
+            x[q] = flip_sign(col[4 * q * L::RB], ((kFoldX >> (4 * q + l)) & 1) ? sx : 0u);
+            nx[q] = make_double2(-x[q].x, -x[q].y);
         }
-        double yr[3], ym[3];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) yr[p] = ym[p] = 0;
-        double2 u[6];
-#pragma unroll
-        for (int pq = 0; pq < 6; ++pq) u[pq] = flip_sign(a[pq], sa);
 #pragma unroll
         for (int q = 0; q < 3; ++q)
 #pragma unroll
             for (int p = 0; p < 3; ++p) {
-                const double2 v = u[pq_index(p, q)];
-                yr[p] = __builtin_amdgcn_mfma_f64_4x4x4f64(v.x, x[q].x, yr[p], 0, 0, 0);
-                ym[p] = __builtin_amdgcn_mfma_f64_4x4x4f64(v.x, x[q].y, ym[p], 0, 0, 0);
-                yr[p] = __builtin_amdgcn_mfma_f64_4x4x4f64(v.y, nx[q], yr[p], 0, 0, 0);
-                ym[p] = __builtin_amdgcn_mfma_f64_4x4x4f64(v.y, x[q].x, ym[p], 0, 0, 0);
+                if (CURL && p == q) continue;
+                const double2 v = op.a[CURL ? curl_k(p, q) : pq_index(p, q)];
+                const bool neg = CURL && curl_neg(p, q);
+                const double2 u = neg ? nx[q] : x[q], w = neg ? x[q] : nx[q];
+                y.r[p] = __builtin_amdgcn_mfma_f64_4x4x4f64(v.x, u.x, y.r[p], 0, 0, 0);
+                y.i[p] = __builtin_amdgcn_mfma_f64_4x4x4f64(v.x, u.y, y.i[p], 0, 0, 0);
+                y.r[p] = __builtin_amdgcn_mfma_f64_4x4x4f64(v.y, w.y, y.r[p], 0, 0, 0);
+                y.i[p] = __builtin_amdgcn_mfma_f64_4x4x4f64(v.y, u.x, y.i[p], 0, 0, 0);
             }
-        if (ok) {
+    }
+    template <bool CURL, int ND>
+    __device__ __forceinline__ void accumulate2(Acc& y0, Acc& y1, const double2* __restrict__ U, int tile, int lane,
+                                                const double2* x0, const double2* x1) const {
+        Op<ND> op;
+        op.load(U, tile, lane);
+        op.fix(lane);
+        accumulate<CURL>(y0, op, x0);
+        accumulate<CURL>(y1, op, x1);
+    }
+    template <bool ODD>
+    __device__ __forceinline__ void store(const Acc& y, double2* buf) const {
+        if (!ok) return;
+        double2* col = buf + off;
 #pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                const unsigned sx = fx ? ((kFoldX >> (4 * p + l)) & 1) << 31 : 0u;
-                col[4 * p * L::RB] = flip_sign(make_double2(yr[p], ym[p]), sx);
-            }
+        for (int p = 0; p < 3; ++p) {
+            const bool f = (((kFoldX >> (4 * p + l)) & 1) != 0) != ODD;
+            col[4 * p * L::RB] = flip_sign(make_double2(y.r[p], y.i[p]), f ? sx : 0u);
         }
     }
 };
 
-template <typename R, int N> struct TileN;
-template <int N> struct TileN<float, N> : TileN32<N> {};
-template <int N> struct TileN<double, N> : TileN64<N> {};
+template <typename R, int N> struct TileOf;
+template <int N> struct TileOf<float, N> { using type = Tile32<N>; };
+template <int N> struct TileOf<double, N> { using type = Tile64<N>; };
+
+// Products of the x pass: N (60 tensors), K (30), or the coupled J-M sums
+//   s_j = N x_j + kj K x_m,  s_m = N x_m + km K x_j
+// over the two halves of a vector pair (rows of the second pair of siblings)
+enum XOp { X_N = 0, X_K = 1, X_JM = 2 };
 
 // where the rows of one workgroup's item live: the two y siblings of one z
-// sibling of an octant row, for one right-hand side
+// sibling of an octant row, for one right-hand side (or both halves of one)
 template <typename R>
 struct XItem {
     bool valid;
     int row, ny_sib;
     unsigned mz;
-    long long off, ystep;   // of row 0, from one y sibling to the other
+    int sz;
+    long long off, ystep, hstep;   // of row 0, from one y sibling or one half to the other
 
-    __device__ __forceinline__ XItem(const P3Params& p, int q, int xcd) {
+    __device__ __forceinline__ XItem(const P3Params& p, int q, int xcd, int halves) {
         // item -> (octant row, right-hand side, z sibling); the 2 nrhs items
         // of one operator row are dealt to one XCD and share its L2
         const int K = 2 * p.nrhs;
         row = (q / K) * 8 + xcd;
-        const int kk = q - (q / K) * K, r = kk >> 1, sz = kk & 1;
+        const int kk = q - (q / K) * K, r = kk >> 1;
+        sz = kk & 1;
         const int oz = row / p.Oy, oy = row - oz * p.Oy;
         ny_sib = (oy == 0 || 2 * oy == p.My) ? 1 : 2;
         valid = row < p.Oy * p.Oz && !(sz && (oz == 0 || 2 * oz == p.Mz));
         mz = sz ? kFoldZ : 0u;
-        off = (long long)r * p.s_r + (long long)(sz ? p.Mz - oz : oz) * p.s_z + (long long)oy * p.s_y;
+        off = (long long)(halves * r) * p.s_r + (long long)(sz ? p.Mz - oz : oz) * p.s_z + (long long)oy * p.s_y;
         ystep = (long long)(p.My - 2 * oy) * p.s_y;
+        hstep = p.s_r;
     }
-    // row t = 12 sy + c: offset, whether it exists, sign bit
-    __device__ __forceinline__ long long at(int t, int s_c, bool& ok, unsigned& sgn) const {
-        const int sy = t >= 12, c = t - 12 * sy;
+    // row t = 24 h + 12 sy + c: offset, whether it exists, sign bit (odd: of
+    // the outputs of an operator that itself changes sign under each fold)
+    __device__ __forceinline__ long long at(int t, int s_c, bool odd, bool& ok, unsigned& sgn) const {
+        const int g = t / 12, c = t - 12 * g, sy = g & 1, h = g >> 1;
         ok = sy < ny_sib;
-        sgn = (((mz ^ (sy ? kFoldY : 0u)) >> c) & 1u) << 31;
-        return off + (sy ? ystep : 0) + c * s_c;
+        sgn = ((((mz ^ (sy ? kFoldY : 0u)) >> c) ^ (odd ? sy ^ sz : 0)) & 1u) << 31;
+        return off + (sy ? ystep : 0) + (h ? hstep : 0) + c * s_c;
     }
 };
 
-template <typename R, int N, int NW>
-__global__ void __launch_bounds__(64 * NW, 3) k_p3_mx(C<R>* __restrict__ A, const C<R>* __restrict__ U, P3Params p,
-                                                        const C<R>* __restrict__ tw) {
-    constexpr int RW = 24 / NW, OX = N / 2 + 1;
-    static_assert(24 % NW == 0, "whole rows per wavefront");
-    using T = TileN<R, N>;
+// U: the 60 N tensors (X_N, X_JM) or the 30 curl tensors (X_K); UK: the curl
+// tensors of X_JM
+template <typename R, int N, int NW, int OP>
+__global__ void __launch_bounds__(64 * NW, 3) k_p3_mx(C<R>* __restrict__ A, const C<R>* __restrict__ U,
+                                                      const C<R>* __restrict__ UK, P3Params p,
+                                                      const C<R>* __restrict__ tw, C<R> kj, C<R> km) {
+    constexpr int H = OP == X_JM ? 2 : 1, RW = 24 * H / NW, OX = N / 2 + 1;
+    static_assert(24 * H % NW == 0, "whole rows per wavefront");
+    using T = typename TileOf<R, N>::type;
+    using L = RowLayout<R, N>;
     extern __shared__ unsigned char smem_raw[];
     C<R>* buf = reinterpret_cast<C<R>*>(smem_raw);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t0 = wave * RW, Nx = p.Nx, s_c = (int)p.s_c;
-    const XItem<R> it(p, blockIdx.x >> 3, blockIdx.x & 7);
+    const XItem<R> it(p, blockIdx.x >> 3, blockIdx.x & 7, H);
     if (!it.valid) return;   // uniform over the workgroup
-    const C<R>* Ur = U + (long long)it.row * 60 * OX;
+    const C<R>* Ur = U + (long long)it.row * (OP == X_K ? 30 : 60) * OX;
     auto load = [&](int t, auto body) {
         bool ok;
         unsigned s;
-        const C<R>* src = A + it.at(t, s_c, ok, s);
+        const C<R>* src = A + it.at(t, s_c, false, ok, s);
         body([=](int c) { return ok && c < Nx ? flip_sign(src[c], s) : mk<R>(0, 0); });
     };
     auto store = [&](int t, auto body) {
         bool ok;
         unsigned s;
-        C<R>* dst = A + it.at(t, s_c, ok, s);
+        C<R>* dst = A + it.at(t, s_c, OP == X_K, ok, s);
         body([=](int c, C<R> v) { if (ok && c < Nx) dst[c] = flip_sign(v, s); });
     };
     RowInputs<R, N, RW> in;
     Twiddles<R, N> w;
-    T tile;
+    [[maybe_unused]] typename T::template Op<OP == X_K ? 3 : 6> op;
     in.fetch(t0, lane, load);
     row_pass<R, true, N, RW, 0>(buf, w, &in, t0, lane, store);
     w.fetch(tw, lane);
     if constexpr (!PassShape<N, 0>::LAST) row_passes<R, true, N, RW, 1>(buf, w, &in, t0, lane, store);
-    if (wave < T::TILES) tile.load(Ur, wave, lane);
+    if (OP != X_JM && wave < T::TILES) op.load(Ur, wave, lane);
     __syncthreads();
     for (int i = wave; i < T::TILES; i += NW) {
-        tile.apply(buf, i, lane, it.ny_sib);
-        if (i + NW < T::TILES) tile.load(Ur, i + NW, lane);
+        const T tile(i, lane, it.ny_sib);
+        if constexpr (OP == X_JM) {
+            // K's sign under the folds of this column, into its factors
+            const unsigned s = (((lane >> 1) ^ lane ^ it.sz) & 1u) << 31;
+            typename T::Acc yj, ym;
+            T::clear(yj);
+            T::clear(ym);
+            tile.template accumulate2<true, 3>(yj, ym, UK + (long long)it.row * 30 * OX, i, lane, buf + L::PAIR, buf);
+            T::scale(yj, flip_sign(kj, s));
+            T::scale(ym, flip_sign(km, s));
+            tile.template accumulate2<false, 6>(yj, ym, Ur, i, lane, buf, buf + L::PAIR);
+            tile.template store<false>(yj, buf);
+            tile.template store<false>(ym, buf + L::PAIR);
+        } else {
+            typename T::Acc y;
+            T::clear(y);
+            op.fix(lane);
+            tile.template accumulate<OP == X_K>(y, op, buf);
+            tile.template store<OP == X_K>(y, buf);
+            if (i + NW < T::TILES) op.load(Ur, i + NW, lane);
+        }
     }
     __syncthreads();
     row_pass<R, false, N, RW, 0>(buf, w, &in, t0, lane, store);
@@ -464,21 +594,33 @@ constexpr int p3_mx_waves() {
     return lane_rounds<N, 4, 0>() < lane_rounds<N, 3, 0>() ? 4 : 3;
 }
 
-template <typename R, int N> constexpr size_t p3_mx_lds() { return (size_t)RowLayout<R, N>::PAIR * sizeof(C<R>); }
-
+// The J-M pass keeps 48 rows, so that fewer workgroups fit: 4 wavefronts (12
+// rows each), more in complex128 where LDS holds one or two workgroups (64^3:
+// 360 us with 4 against 553 with 6 in complex64; complex128 48^3 263 with 4
+// against 216 with 8, 72 x 61 x 85 1468 against 868 with 12).
 template <typename R, int N>
-void launch_p3_mx_n(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s) {
-    constexpr int NW = p3_mx_waves<R, N>();
-    const size_t lds = p3_mx_lds<R, N>();
+constexpr int p3_mx_jm_waves() {
+    return sizeof(R) == 4 || N <= 64 ? 4 : N <= 100 ? 8 : 12;
+}
+
+template <typename R, int N> constexpr size_t p3_mx_lds(int halves = 1) {
+    return (size_t)halves * RowLayout<R, N>::PAIR * sizeof(C<R>);
+}
+
+template <typename R, int N, int OP, int NW = OP == X_JM ? p3_mx_jm_waves<R, N>() : p3_mx_waves<R, N>()>
+void launch_p3_mx_n(C<R>* A, const C<R>* U, const C<R>* UK, const P3Params& p, const C<R>* tw, C<R> kj, C<R> km,
+                    hipStream_t s) {
+    const size_t lds = p3_mx_lds<R, N>(OP == X_JM ? 2 : 1);
     const long long nblk = ((long long)p.Oy * p.Oz + 7) / 8 * 8 * 2LL * p.nrhs;
     VIE_REQUIRE(nblk < (1LL << 31), VIE_EINVAL, "x pass: too many workgroups");
     static std::once_flag once;
     std::call_once(once, [&] {
-        (void)hipFuncSetAttribute((const void*)k_p3_mx<R, N, NW>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute((const void*)k_p3_mx<R, N, NW, OP>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds);
         (void)hipGetLastError();
     });
-    timed_launch(k_p3_mx<R, N, NW>, dim3((unsigned)nblk), dim3(64 * NW), (unsigned)lds, s, A, U, p, tw);
+    timed_launch(k_p3_mx<R, N, NW, OP>, dim3((unsigned)nblk), dim3(64 * NW), (unsigned)lds, s, A, U, UK, p, tw, kj,
+                 km);
     VIE_HIP(hipGetLastError());
 }
 

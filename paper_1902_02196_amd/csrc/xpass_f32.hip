@@ -9,7 +9,7 @@ bool launch_p3_mx<float>(C<float>* A, const C<float>* U, const P3Params& p, cons
     switch (p.plan.n) {
 #define CASE(n_)                                          \
     case n_:                                             \
-        launch_p3_mx_n<float, n_>(A, U, p, tw, s);    \
+        launch_p3_mx_n<float, n_, X_N>(A, U, nullptr, p, tw, {}, {}, s);    \
         return true;
         VIE_MIX_LENGTHS(CASE)
 #undef CASE

@@ -19,7 +19,7 @@ bool launch_p3_mx<double>(C<double>* A, const C<double>* U, const P3Params& p, c
     switch (p.plan.n) {
 #define CASE(n_)                                          \
     case n_:                                             \
-        launch_p3_mx_n<double, n_>(A, U, p, tw, s);   \
+        launch_p3_mx_n<double, n_, X_N>(A, U, nullptr, p, tw, {}, {}, s);   \
         return true;
         VIE_MIX_LENGTHS(CASE)
 #undef CASE

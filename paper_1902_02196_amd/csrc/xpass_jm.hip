@@ -1,0 +1,54 @@
+// Matrix-core x pass of the J-M product, both precisions (xpass.hpp).
+#include "xpass.hpp"
+
+namespace vie {
+
+// Lengths it takes: those whose 48 rows fit LDS, except the ones where the
+// kernel with one fused multiply-add per entry and 24 rows per workgroup is
+// faster (complex64 128: 322 us against 360 at 64^3, 192: 1174 against 1411
+// at 96^3, complex128 128: 602 against 652); at the others this one wins
+// (complex64 48^3 188 -> 133, 72 x 61 x 85 3317 -> 729, complex128 32^3
+// 188 -> 59).
+template <typename R, int N> constexpr bool jm_fits() {
+    constexpr bool vec = sizeof(R) == 4 ? N == 128 || N == 160 || N == 192 || N == 256 || N >= 320 : N == 128;
+    return !vec && p3_mx_lds<R, N>(2) <= 160 * 1024;
+}
+
+bool p3_mx_jm_fits(int es, int n) {
+    switch (n) {
+#define CASE(n_) \
+    case n_: return es == 8 ? jm_fits<float, n_>() : jm_fits<double, n_>();
+        VIE_MIX_LENGTHS(CASE)
+#undef CASE
+        default: return false;
+    }
+}
+
+template <typename R>
+static bool launch_jm(C<R>* A, const C<R>* UN, const C<R>* UK, const P3Params& p, const C<R>* tw, C<R> kj, C<R> km,
+                      hipStream_t s) {
+    if (!p3_mx_jm_fits((int)sizeof(C<R>), p.plan.n) || 2 * p.Nx > p.plan.n) return false;
+    switch (p.plan.n) {
+#define CASE(n_)                                                                    \
+    case n_:                                                                       \
+        if constexpr (jm_fits<R, n_>())                                            \
+            launch_p3_mx_n<R, n_, X_JM>(A, UN, UK, p, tw, kj, km, s);              \
+        return true;
+        VIE_MIX_LENGTHS(CASE)
+#undef CASE
+        default: return false;
+    }
+}
+
+template <>
+bool launch_p3_mx_jm<float>(C<float>* A, const C<float>* UN, const C<float>* UK, const P3Params& p,
+                            const C<float>* tw, C<float> kj, C<float> km, hipStream_t s) {
+    return launch_jm<float>(A, UN, UK, p, tw, kj, km, s);
+}
+template <>
+bool launch_p3_mx_jm<double>(C<double>* A, const C<double>* UN, const C<double>* UK, const P3Params& p,
+                             const C<double>* tw, C<double> kj, C<double> km, hipStream_t s) {
+    return launch_jm<double>(A, UN, UK, p, tw, kj, km, s);
+}
+
+}  // namespace vie

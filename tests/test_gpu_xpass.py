@@ -60,26 +60,42 @@ def _unique_index():
     return out
 
 
-def reference(torch, T, x):
-    """N x by the circulant of 2 N per axis, complex128; T [60, Nz, Ny, Nx], x [n, 12, Nz, Ny, Nx]."""
+def _circulant(torch, T, members, reflect, x):
+    """The 12 x 12 block circulant product, complex128: T [n, Nz, Ny, Nx] unique
+    tensors, members {(a, b): (tensor, sign)}, reflect(tensor, axis) the sign of
+    its mirror, x [nrhs, 12, Nz, Ny, Nx]."""
     Nz, Ny, Nx = T.shape[1:]
-    M = (2 * Nz, 2 * Ny, 2 * Nx)
     spec = []
-    for a, b in UNIQUE_AB:
-        C = torch.zeros(M, dtype=torch.complex128, device="cuda")
-        t = T[len(spec)]
+    for e in range(T.shape[0]):
+        t = T[e]
         for dim, axis, n in ((0, 2, Nz), (1, 1, Ny), (2, 0, Nx)):
-            mirror = _sign(axis, a) * _sign(axis, b) * t.narrow(dim, 1, n - 1).flip(dim)
-            gap = torch.zeros_like(t.narrow(dim, 0, 1))
-            t = torch.cat([t, gap, mirror], dim)
-        C.copy_(t)
-        spec.append(torch.fft.fftn(C))
-    X = torch.fft.fftn(x.to(torch.complex128), s=M, dim=(2, 3, 4))
-    idx = _unique_index()
+            mirror = reflect(e, axis) * t.narrow(dim, 1, n - 1).flip(dim)
+            t = torch.cat([t, torch.zeros_like(t.narrow(dim, 0, 1)), mirror], dim)
+        spec.append(torch.fft.fftn(t))
+    X = torch.fft.fftn(x.to(torch.complex128), s=(2 * Nz, 2 * Ny, 2 * Nx), dim=(2, 3, 4))
     Y = torch.zeros_like(X)
-    for (a, b), (e, s) in idx.items():
+    for (a, b), (e, s) in members.items():
         Y[:, a] += s * spec[e] * X[:, b]
     return torch.fft.ifftn(Y, dim=(2, 3, 4))[:, :, :Nz, :Ny, :Nx]
+
+
+def reference(torch, T, x):
+    """N x from the 60 block tensors."""
+    return _circulant(torch, T, _unique_index(),
+                      lambda e, i: _sign(i, UNIQUE_AB[e][0]) * _sign(i, UNIQUE_AB[e][1]), x)
+
+
+def curl_reference(torch, TK, x):
+    """K x from the 30 curl tensors: K^{pl,ql'} = eps_pkq Q_k^{ll'}, mirrored
+    with -sigma_i(a) sigma_i(b)."""
+    members, rep = {}, {}
+    for (a, b), (e, s) in _unique_index().items():
+        p, q = a // 4, b // 4
+        if p != q:
+            k = 3 - p - q
+            members[a, b] = (10 * k + e % 10, s * (1 if (k - p) % 3 == 1 else -1))
+            rep[10 * k + e % 10] = (a, b)
+    return _circulant(torch, TK, members, lambda e, i: -_sign(i, rep[e][0]) * _sign(i, rep[e][1]), x)
 
 
 @pytest.mark.parametrize("M", LENGTHS)
@@ -100,9 +116,66 @@ def test_every_length(vie, torch, M):
             except vie.VieError:
                 assert prec == vie.C128 and M == 512   # its rows do not fit LDS
                 continue
+            if prec == vie.C128 and M in (240, 250):
+                with pytest.raises(vie.VieError):   # lengths the complex128 product has never taken
+                    c.apply(x, torch.empty_like(x), op=vie.OP_N)
+                continue
             xd = x.to(dtype).contiguous()
             y = torch.full_like(xd, float("nan"))
             c.apply(xd, y, op=vie.OP_N)
             r = ref if dtype == torch.complex128 else reference(torch, T, xd)
             err = ((y.to(torch.complex128) - r).norm() / r.norm()).item()
             assert err < 50 * eps, (N, dtype, err)
+
+
+def _random(torch, g, shape):
+    return torch.view_as_complex(torch.randn(tuple(shape) + (2,), generator=g, device="cuda", dtype=torch.float64))
+
+
+@pytest.mark.parametrize("M", [n for n in LENGTHS if n <= 256])
+def test_curl_and_coupled_products(vie, torch, M):
+    """The curl operator's product (magnetic field, complex128) and the coupled
+    sums of the J-M product (A x, both precisions) at every length they take."""
+    w = 2 * np.pi * F
+    ce, cm = 1j * w * 8.8541878128e-12, 1j * w * 1.25663706212e-6
+    dv = 0.003 * 0.004 * 0.005
+    for N in ((M // 2, 3, 2), (max(1, M // 2 - 3), 2, 3)):
+        g = torch.Generator(device="cuda").manual_seed(M)
+        fft = (M, 2 * N[1], 2 * N[2])
+        c = vie.Context(0)
+        c.set_grid(N, (0.003, 0.004, 0.005), F, fft_size=fft)
+        T = torch.from_numpy(c.get_toeplitz()).cuda()
+        TK = torch.from_numpy(c.get_curl_toeplitz()).cuda()
+        G = torch.tensor([dv, dv / 12, dv / 12, dv / 12] * 3, device="cuda", dtype=torch.float64).view(1, 12, 1, 1, 1)
+        x, ht = _random(torch, g, c.vec_shape(2)), torch.zeros(c.vec_shape(2), dtype=torch.complex128, device="cuda")
+        h = torch.full_like(x, float("nan"))
+        print("M %d N %s curl" % (M, N), flush=True)
+        c.magnetic_field(ht, x, h)
+        r = curl_reference(torch, TK, x) / G
+        err = ((h - r).norm() / r.norm()).item()
+        assert err < 50 * 1.2e-16, (N, err)
+
+        c = vie.Context(0)
+        c.set_basis(24)
+        c.set_grid(N, (0.003, 0.004, 0.005), F, fft_size=fft)
+        shape = x.shape[2:]
+        eps, sig, mu, mi = (torch.rand(shape, generator=g, device="cuda", dtype=torch.float64) for _ in range(4))
+        eps, mu = 1 + 40 * eps, 1 + 2 * mu
+        c.set_contrast(eps, sig)
+        c.set_magnetic_contrast(mu.cpu().numpy(), mi.cpu().numpy())
+        er, mr = torch.complex(eps, -sig / (w * 8.8541878128e-12)), torch.complex(mu, -mi)
+        x = _random(torch, g, c.vec_shape(2))
+        x[:, 12:] *= 1e-3   # magnetic currents are of another size: both couplings count
+        for dtype, e in ((torch.complex64, 6e-8), (torch.complex128, 1.2e-16)):
+            print("M %d N %s J-M %s" % (M, N, dtype), flush=True)
+            if dtype == torch.complex128 and M in (240, 250):
+                continue   # complex128 takes no PWL product of these lengths
+            xd = x.to(dtype).contiguous()
+            y = torch.full_like(xd, float("nan"))
+            c.apply(xd, y, op=vie.OP_A)
+            xj, xm = xd[:, :12].to(torch.complex128), xd[:, 12:].to(torch.complex128)
+            rj = er * G * xj - (er - 1) * (reference(torch, T, xj) - ce * curl_reference(torch, TK, xm))
+            rm = mr * G * xm - (mr - 1) * (reference(torch, T, xm) + cm * curl_reference(torch, TK, xj))
+            for part, r in ((y[:, :12], rj), (y[:, 12:], rm)):
+                err = ((part.to(torch.complex128) - r).norm() / r.norm()).item()
+                assert err < 50 * e, (N, dtype, err)
