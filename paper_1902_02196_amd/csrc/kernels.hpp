@@ -240,8 +240,13 @@ void launch_triple_coef(double2* tc, const double* gpart, int nblocks, int nrhs,
 template <typename R>
 void launch_axpy_triple(C<R>* u1, long long ldv, long long n, long long rstride, const double2* tc, double* np2,
                         double* np3, int nrhs, int nblocks, hipStream_t s);
-void launch_triple_columns(ArnoldiState st, const double2* g, long long gst, const double2* tc, double2* col1,
-                           double2* col2, int j, int na, hipStream_t s);
+// columns j .. j + 2 of a triple folded into the rotations (np1..3: norm
+// partials of u_{j+1..j+3}, their reciprocal norms to ivn[s * ivn_ld + 0..2]),
+// the stop flags as after three launch_givens; tail: scratch [na][kTripleTail]
+constexpr int kTripleTail = 10;
+void launch_triple_finish(ArnoldiState st, const double2* g, long long gst, const double2* tc, const double* np1,
+                          const double* np2, const double* np3, int nblocks, double* ivn, long long ivn_ld,
+                          double2* tail, int j, int na, hipStream_t s);
 // y = R^-1 g over the first nvec columns, scaled by the basis vectors'
 // reciprocal norms (the coefficients of the stored vectors), y [na][nvec]
 void launch_backsolve(ArnoldiState st, const double* ivn, long long ivn_ld, double2* y, int nvec, int na,

@@ -883,76 +883,6 @@ void launch_axpy_triple(C<R>* u1, long long ldv, long long n, long long rs, cons
     VIE_HIP(hipGetLastError());
 }
 
-// Hessenberg columns j + 1 (entries 0..j + 1) and j + 2 (entries 0..j + 2)
-// of a triple into col1 [na][j + 2] and col2 [na][j + 3] (the subdiagonal
-// entries come from the stored norms): one workgroup of 4 waves per slot,
-// the products A V g1 and A V g2 over the unrotated columns 0..j summed by
-// the waves in LDS in a fixed order, then wave 0 forms the entries
-__global__ void __launch_bounds__(64 * kColWaves) k_triple_columns(ArnoldiState st, const double2* __restrict__ g,
-                                                                   long long gst, const double2* __restrict__ tc,
-                                                                   double2* __restrict__ col1,
-                                                                   double2* __restrict__ col2, int j) {
-    __shared__ double2 part[2][kColWaves][kColRows];
-    const int r = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6, m = st.m, nvec = j + 1;
-    const double2* g1 = g + (long long)r * nvec;
-    const double2* g2 = g1 + gst;
-    const double2* g3 = g2 + gst;
-    const double2* Hr = st.Hr + (long long)r * m * (m + 1);
-    for (int i = lane; i <= j + 1; i += 64) {
-        double2 a1 = make_double2(0.0, 0.0), a2 = make_double2(0.0, 0.0);
-#pragma unroll 4
-        for (int k = wv; k <= j; k += kColWaves)
-            if (k >= i - 1) {
-                const double2 hk = Hr[(long long)k * (m + 1) + i];
-                a1 = cadd(a1, cmul(hk, g1[k]));
-                a2 = cadd(a2, cmul(hk, g2[k]));
-            }
-        part[0][wv][i] = a1;
-        part[1][wv][i] = a2;
-    }
-    __syncthreads();
-    if (wv == 0) {
-        const double2* t = tc + 8 * r;
-        const double r11 = t[0].x, r22 = t[0].y, i11 = t[4].x, i22 = t[4].y;
-        const double2 r12 = t[1], r13 = t[2], r23 = t[3];
-        const double2 sg = g1[j];
-        double2* o1 = col1 + (long long)r * (j + 2);   // the strides the Givens kernel reads
-        double2* o2 = col2 + (long long)r * (j + 3);
-        for (int i = lane; i <= j + 1; i += 64) {
-            double2 hv1 = part[0][0][i], hv2 = part[1][0][i];
-            for (int w = 1; w < kColWaves; ++w) {
-                hv1 = cadd(hv1, part[0][w][i]);
-                hv2 = cadd(hv2, part[1][w][i]);
-            }
-            // column j + 1, row i: (z2 + sigma z1 - A V g1)_i / R11
-            double2 c1;
-            if (i <= j) c1 = cscale(csub(cadd(g2[i], cmul(sg, g1[i])), hv1), i11);
-            else c1 = cscale(r12, i11);   // row j + 1: R12 / R11
-            o1[i] = c1;
-            // column j + 2, row i: (z3 + sigma z2 - A V g2 - R12 A q1)_i / R22
-            double2 c2;
-            if (i <= j) c2 = csub(cadd(g3[i], cmul(sg, g2[i])), hv2);
-            else c2 = csub(cadd(r13, cmul(sg, r12)), hv2);   // row j + 1 (z1 has no q1 part beyond R11)
-            c2 = csub(c2, cmul(r12, c1));
-            o2[i] = cscale(c2, i22);
-        }
-        if (lane == 0) {
-            // column j + 2, row j + 2: (R23 + sigma R22 - R12 (A q1)_{j+2}) / R22, (A q1)_{j+2} = R22 / R11
-            const double2 aq = make_double2(r22 * i11, 0.0);
-            o2[j + 2] = cscale(csub(cadd(r23, cscale(sg, r22)), cmul(r12, aq)), i22);
-        }
-        (void)r11;
-    }
-}
-
-void launch_triple_columns(ArnoldiState st, const double2* g, long long gst, const double2* tc, double2* col1,
-                           double2* col2, int j, int na, hipStream_t s) {
-    VIE_REQUIRE(st.Hr != nullptr && j + 2 < st.m && j + 2 < kColRows, VIE_EINVAL,
-                "triple columns without the unrotated Hessenberg matrix");
-    hipLaunchKernelGGL(k_triple_columns, dim3(na), dim3(64 * kColWaves), 0, s, st, g, gst, tc, col1, col2, j);
-    VIE_HIP(hipGetLastError());
-}
-
 // norms from partial sums of squares; with inv != nullptr also their
 // reciprocals (0 for a zero norm) at inv[r * inv_ld]
 __global__ void k_reduce_norm(double* __restrict__ out, const double* __restrict__ partial, int nblocks,
@@ -1175,6 +1105,220 @@ void launch_givens(ArnoldiState st, const double2* h1, const double2* h2, const 
     VIE_REQUIRE(j >= 0 && j + 1 < kGivRows && j < st.m, VIE_EINVAL, "Givens column beyond restart 200");
     hipLaunchKernelGGL(k_givens, dim3(1), dim3(64 * kGivWaves), 0, s, st, h1, h2, npart, nblocks, nrm, ivn_next,
                        ivn_ld, j, na);
+    VIE_HIP(hipGetLastError());
+}
+
+// The three columns of a triple in one launch: the norms of u_{j+1..j+3} and
+// their reciprocals, the Hessenberg columns j (g1), j + 1 and j + 2 (from g,
+// tc and the products A V g1, A V g2 over the unrotated columns 0..j), the
+// rotations and the stop flags, as three runs of k_givens would set them.
+//
+// One workgroup; groups of 4 waves take a slot each.  Waves 0..2 of a group
+// sum one norm, all four the products over their columns k; then wave 0 forms
+// the columns and its lanes 0..2 apply the rotations 0..j - 1 to one column
+// each, side by side.  What couples the columns (rotations j .. j + 2, at most
+// 3 per column) and the slots (the stop flags) is left to one wave at the end,
+// a lane per slot, from the few values per slot in tail.
+//
+// All of it is latency: the serial chain of the rotations, of which one is
+// left instead of three, and launches, one instead of four (28 us together;
+// this kernel 9.9 at 16^3, 13.4 at 64^3 PWC with its longer norm sums).
+constexpr int kTailLds = 64;   // slots whose tail fits LDS, else global memory
+// per slot kTripleTail values: a0; a1, b1; a2, b2, c2; (h0, h1); (h2, 0); g; (norm, target)
+__host__ __device__ constexpr size_t triple_rows_bytes(int m) { return (size_t)(2 * kColWaves + 5) * (m + 2) * 16; }
+
+template <bool BIG>
+__global__ void __launch_bounds__(64 * kColWaves * 4) k_triple_finish(
+    ArnoldiState st, const double2* __restrict__ gc, long long gst, const double2* __restrict__ tc,
+    const double* __restrict__ np1, const double* __restrict__ np2, const double* __restrict__ np3, int nblocks,
+    double* __restrict__ ivn, long long ivn_ld, double2* __restrict__ tail_g, int j, int na) {
+    extern __shared__ double2 sh[];
+    __shared__ double hnl[4][3];
+    const int m = st.m, rows = m + 2, ng = blockDim.x / (64 * kColWaves);
+    const int grp = threadIdx.x / (64 * kColWaves), wv = (threadIdx.x >> 6) % kColWaves, lane = threadIdx.x & 63;
+    double2* part = sh + (size_t)grp * (2 * kColWaves + 5) * rows;   // [2][kColWaves][rows]
+    double2* lh = part + 2 * kColWaves * rows;                       // [3][rows]
+    double2 *lc = lh + 3 * rows, *ls = lc + rows;
+    double2* tail = BIG ? tail_g : sh + (size_t)ng * (2 * kColWaves + 5) * rows;
+    const bool stopped = st.status[1] | st.status[2];   // uniform: stopped at an earlier column
+    const int nvec = j + 1;
+    for (int base = 0; base < na; base += ng) {   // the same trip count in every wave
+        const int s = base + grp;
+        const double2* g1 = gc + (long long)s * nvec;
+        const double2 *g2 = g1 + gst, *g3 = g2 + gst;
+        double2* Hr = st.Hr + (long long)s * m * (m + 1);
+        if (s < na) {
+            if (wv < 3) {
+                const double* np = (wv == 0 ? np1 : wv == 1 ? np2 : np3) + (long long)s * nblocks;
+                double q = 0;
+#pragma unroll 8
+                for (int b = lane; b < nblocks; b += 64) q += np[b];
+                q = wave_sum(q);
+                if (lane == 0) {
+                    const double nv = sqrt(q);
+                    ivn[s * ivn_ld + wv] = nv > 0 ? 1.0 / nv : 0.0;
+                    hnl[grp][wv] = nv;
+                }
+            }
+            if (!stopped) {
+                if (wv == 3)
+                    for (int i = lane; i <= j; i += 64) {
+                        lh[i] = g1[i];
+                        if (i < j) {
+                            lc[i] = st.cs[(long long)s * m + i];
+                            ls[i] = st.sn[(long long)s * m + i];
+                        }
+                    }
+                for (int i = lane; i <= j; i += 64) {
+                    double2 a1 = make_double2(0.0, 0.0), a2 = make_double2(0.0, 0.0);
+#pragma unroll 4
+                    for (int k = wv; k < j; k += kColWaves)
+                        if (k >= i - 1) {
+                            const double2 hk = Hr[(long long)k * (m + 1) + i];
+                            a1 = cadd(a1, cmul(hk, g1[k]));
+                            a2 = cadd(a2, cmul(hk, g2[k]));
+                        }
+                    part[wv * rows + i] = a1;
+                    part[(kColWaves + wv) * rows + i] = a2;
+                }
+            }
+        }
+        __syncthreads();
+        if (s < na && !stopped && wv == 0) {
+            const double2* t = tc + 8 * s;
+            const double r22 = t[0].y, i11 = t[4].x, i22 = t[4].y;
+            const double2 r12 = t[1], r13 = t[2], r23 = t[3];
+            const double2 sg = g1[j], g2j = g2[j];
+            const double h0 = hnl[grp][0], h1 = hnl[grp][1], h2 = hnl[grp][2];
+            double2 *Hu0 = Hr + (long long)j * (m + 1), *Hu1 = Hu0 + (m + 1), *Hu2 = Hu1 + (m + 1);
+            for (int i = lane; i <= j + 1; i += 64) {
+                // column j of A V: g1 above the subdiagonal, the norm below
+                const double2 hj = i <= j ? lh[i] : make_double2(h0, 0.0);
+                double2 hv1 = cmul(hj, sg), hv2 = cmul(hj, g2j);
+                if (i <= j)
+                    for (int w = 0; w < kColWaves; ++w) {
+                        hv1 = cadd(hv1, part[w * rows + i]);
+                        hv2 = cadd(hv2, part[(kColWaves + w) * rows + i]);
+                    }
+                // column j + 1, row i: (z2 + sigma z1 - A V g1)_i / R11; row j + 1: R12 / R11
+                const double2 c1 = i <= j ? cscale(csub(cadd(g2[i], cmul(sg, hj)), hv1), i11) : cscale(r12, i11);
+                // column j + 2, row i: (z3 + sigma z2 - A V g2 - R12 A q1)_i / R22
+                // (row j + 1: z1 has no q1 part beyond R11)
+                double2 c2 = i <= j ? csub(cadd(g3[i], cmul(sg, g2[i])), hv2)
+                                    : csub(cadd(r13, cmul(sg, r12)), hv2);
+                c2 = cscale(csub(c2, cmul(r12, c1)), i22);
+                lh[rows + i] = c1;
+                lh[2 * rows + i] = c2;
+                Hu0[i] = hj;
+                Hu1[i] = c1;
+                Hu2[i] = c2;
+            }
+            if (lane == 0) {
+                // column j + 2, row j + 2: (R23 + sigma R22 - R12 (A q1)_{j+2}) / R22, (A q1)_{j+2} = R22 / R11
+                const double2 aq = make_double2(r22 * i11, 0.0);
+                const double2 c2 = cscale(csub(cadd(r23, cscale(sg, r22)), cmul(r12, aq)), i22);
+                lh[2 * rows + j + 2] = c2;
+                Hu1[j + 2] = make_double2(h1, 0.0);
+                Hu2[j + 2] = c2;
+                Hu2[j + 3] = make_double2(h2, 0.0);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (lane < 3) {   // rotations 0..j - 1: (a, b) <- (c a + z b, conj(c) b - conj(z) a)
+                const double2* l = lh + lane * rows;
+                double2* Hc = st.H + ((long long)s * m + j + lane) * (m + 1);
+                double2 a = l[0];
+#pragma unroll 4
+                for (int i = 0; i < j; ++i) {
+                    const double2 b = l[i + 1], c = lc[i], z = ls[i];
+                    Hc[i] = cadd(cmul(c, a), cmul(z, b));
+                    a = csub(cmulc(c, b), cmulc(z, a));
+                }
+                double2* tl = tail + kTripleTail * s;
+                tl[lane == 0 ? 0 : lane == 1 ? 1 : 3] = a;
+                if (lane == 1) tl[2] = l[j + 1];
+                if (lane == 2) {
+                    tl[4] = l[j + 1];
+                    tl[5] = l[j + 2];
+                }
+            } else if (lane == 3) {
+                double2* tl = tail + kTripleTail * s;
+                tl[6] = make_double2(h0, h1);
+                tl[7] = make_double2(h2, 0.0);
+                tl[8] = st.g[(long long)s * (m + 1) + j];
+                tl[9] = st.slot[s];
+            }
+        }
+        __syncthreads();   // the LDS rows are reused by the next round
+    }
+    if (stopped || threadIdx.x >= 64) return;
+    for (int q = 0; q < 3; ++q) {   // column j + q of every slot, a lane each
+        bool open = false, bad = false;
+        for (int s = lane; s < na; s += 64) {
+            double2* tl = tail + kTripleTail * s;
+            const double2 a = tl[q == 0 ? 0 : q == 1 ? 1 : 3];
+            const double hn = q == 0 ? tl[6].x : q == 1 ? tl[6].y : tl[7].x;
+            const double den = sqrt(a.x * a.x + a.y * a.y + hn * hn);
+            double2 c, z;
+            if (den == 0.0) {
+                c = make_double2(1.0, 0.0);
+                z = make_double2(0.0, 0.0);
+            } else {
+                c = make_double2(a.x / den, -a.y / den);   // conj(a) / den
+                z = make_double2(hn / den, 0.0);
+            }
+            const int jq = j + q;
+            double2* Hc = st.H + ((long long)s * m + jq) * (m + 1);
+            Hc[jq] = make_double2(den, 0.0);
+            Hc[jq + 1] = make_double2(0.0, 0.0);
+            st.cs[(long long)s * m + jq] = c;
+            st.sn[(long long)s * m + jq] = z;
+            if (q == 0) {
+                const double2 x = tl[1], y = tl[2];
+                Hc[m + 1 + jq] = cadd(cmul(c, x), cmul(z, y));
+                tl[1] = csub(cmulc(c, y), cmulc(z, x));
+            }
+            if (q < 2) {
+                const double2 x = tl[3], y = tl[4 + q];
+                Hc[(2 - q) * (m + 1) + jq] = cadd(cmul(c, x), cmul(z, y));
+                tl[3] = csub(cmulc(c, y), cmulc(z, x));
+            }
+            double2* g = st.g + (long long)s * (m + 1);
+            const double2 gj = tl[8], sl = tl[9];
+            const double2 gn = make_double2(-(z.x * gj.x + z.y * gj.y), -(z.x * gj.y - z.y * gj.x));   // -conj(z) g_j
+            g[jq + 1] = gn;
+            g[jq] = cmul(c, gj);
+            tl[8] = gn;
+            const double est = sqrt(gn.x * gn.x + gn.y * gn.y) / sl.x;
+            if (!isfinite(est)) bad = true;
+            if (!(est <= sl.y) && hn > 0.0) open = true;
+        }
+        const bool any_open = __any(open), any_bad = __any(bad);
+        if (lane == 0) {
+            st.status[0] = j + q + 1;
+            if (any_bad) st.status[2] = 1;
+            if (!any_open) st.status[1] = 1;
+        }
+        if (any_bad || !any_open) break;
+    }
+}
+
+void launch_triple_finish(ArnoldiState st, const double2* g, long long gst, const double2* tc, const double* np1,
+                          const double* np2, const double* np3, int nblocks, double* ivn, long long ivn_ld,
+                          double2* tail, int j, int na, hipStream_t s) {
+    VIE_REQUIRE(st.Hr != nullptr && j >= 0 && j + 2 < st.m && j + 2 < kColRows, VIE_EINVAL,
+                "triple columns without the unrotated Hessenberg matrix");
+    // groups of 4 waves, as many as 60 KB of LDS hold (restart 50: 4, 200: 1)
+    const size_t rb = triple_rows_bytes(st.m), tb = na <= kTailLds ? (size_t)na * kTripleTail * 16 : 0;
+    int ng = na < 4 ? na : 4;
+    while (ng > 1 && ng * rb + tb > 60 * 1024) --ng;
+    const dim3 nt(64 * kColWaves * ng);
+    if (na <= kTailLds)
+        hipLaunchKernelGGL(k_triple_finish<false>, dim3(1), nt, ng * rb + tb, s, st, g, gst, tc, np1, np2, np3, nblocks,
+                           ivn, ivn_ld, tail, j, na);
+    else
+        hipLaunchKernelGGL(k_triple_finish<true>, dim3(1), nt, ng * rb, s, st, g, gst, tc, np1, np2, np3, nblocks, ivn,
+                           ivn_ld, tail, j, na);
     VIE_HIP(hipGetLastError());
 }
 

@@ -63,9 +63,9 @@ struct Layout {
     double2 *Hr, *coef2, *dpart, *pc, *col;
     double* npart2;
     // three-step Arnoldi: g_1..3 and their coefficients (3 [na][m + 1]
-    // blocks each), Gram partials, Cholesky coefficients, the two assembled
-    // columns, norm partials of u_{j+3}
-    double2 *g3, *coef3, *tc, *col2;
+    // blocks each), Gram partials, Cholesky coefficients, the values of the
+    // columns' last rows, norm partials of u_{j+3}
+    double2 *g3, *coef3, *tc, *tail;
     double *gpart, *npart3;
 };
 
@@ -237,15 +237,13 @@ static int run(Ctx& c, const vie_solve_opts& o, int nrhs, double2* x, const Layo
                 launch_update_triple<R>(w1, Vb, ldv, nvec, L.coef3, gst, L.g3, n, n, n, L.npart, L.gpart, L.ivn, ivld,
                                         j, na, nb, c.stream);
             }
-            launch_givens(as, L.g3, nullptr, L.npart, nb, L.nrm, L.ivn + (j + 1), ivld, j, na, c.stream);
             launch_triple_coef(L.tc, L.gpart, nb, na, c.stream);
             {   // reads y1..y3, writes u_{j+2}, u_{j+3}
                 ProfScope ps(c.prof, c.stream, VIE_K_GS_PAIR, vb * 5);
                 launch_axpy_triple<R>(w1, ldv, n, n, L.tc, L.npart2, L.npart3, na, nb, c.stream);
             }
-            launch_triple_columns(as, L.g3, gst, L.tc, L.col, L.col2, j, na, c.stream);
-            launch_givens(as, L.col, nullptr, L.npart2, nb, L.nrm, L.ivn + (j + 2), ivld, j + 1, na, c.stream);
-            launch_givens(as, L.col2, nullptr, L.npart3, nb, L.nrm, L.ivn + (j + 3), ivld, j + 2, na, c.stream);
+            launch_triple_finish(as, L.g3, gst, L.tc, L.npart, L.npart2, L.npart3, nb, L.ivn + (j + 1), ivld, L.tail, j,
+                                 na, c.stream);
         };
         // s = 3 by default (pairs and single steps fill the end of a
         // cycle), 2 or 1 on request; the second Gram-Schmidt pass runs with
@@ -403,7 +401,7 @@ int solve(Ctx& c, const vie_solve_opts& o, int nrhs, const double2* et, double2*
     const size_t o_dp = take((size_t)nrhs * nb * 16), o_pc = take((size_t)nrhs * 2 * 16);
     const size_t o_col = take((size_t)nrhs * (m + 1) * 16), o_np2 = take((size_t)nrhs * nb * 8);
     const size_t o_g3 = take((size_t)3 * nrhs * (m + 1) * 16), o_coef3 = take((size_t)3 * nrhs * (m + 1) * 16);
-    const size_t o_tc = take((size_t)nrhs * 8 * 16), o_col2 = take((size_t)nrhs * (m + 2) * 16);
+    const size_t o_tc = take((size_t)nrhs * 8 * 16), o_tail = take((size_t)nrhs * kTripleTail * 16);
     const size_t o_gp = take((size_t)nrhs * nb * 8 * 8), o_np3 = take((size_t)nrhs * nb * 8);
     char* base = static_cast<char*>(c.vecs.get(off));
     Layout L{};
@@ -435,7 +433,7 @@ int solve(Ctx& c, const vie_solve_opts& o, int nrhs, const double2* et, double2*
     L.g3 = reinterpret_cast<double2*>(base + o_g3);
     L.coef3 = reinterpret_cast<double2*>(base + o_coef3);
     L.tc = reinterpret_cast<double2*>(base + o_tc);
-    L.col2 = reinterpret_cast<double2*>(base + o_col2);
+    L.tail = reinterpret_cast<double2*>(base + o_tail);
     L.gpart = reinterpret_cast<double*>(base + o_gp);
     L.npart3 = reinterpret_cast<double*>(base + o_np3);
     if (st)

@@ -196,6 +196,42 @@ def test_two_step_arnoldi_matches_one_step(vie, torch, mode, restart):
         assert abs(a - b) <= max(4, 0.15 * a)
 
 
+@pytest.mark.parametrize("nrhs,restart", [(1, 3), (1, 50), (3, 4), (5, 50), (9, 200), (70, 12), (66, 160)])
+def test_three_step_columns_over_slots(vie, torch, nrhs, restart):
+    """The columns of three Arnoldi steps are folded in by one launch, whose
+    groups of waves take a slot each (1 to 4 of them, by the restart length)
+    and whose last part keeps up to 64 slots in LDS: random right-hand sides
+    on either side of these counts, against dense LU and the step count of
+    two-step Arnoldi, whose columns are folded in one by one.  (One step at
+    a time loses orthogonality past 100 vectors and takes a second cycle.)
+    A relative residual of 1e-11 bounds the error by the condition number
+    (below 1e3 here) times that."""
+    N, D = (3, 2, 3), (0.005, 0.006, 0.005)
+    _say("three-step columns nrhs %d restart %d" % (nrhs, restart))
+    T = _blocks(N, D)
+    e, s = vi.ellipsoid_phantom(N, D, 75)
+    tau, chi = physics.tau(e, s, F), physics.chi(e, s, F)
+    ets = [vi.complex_normal(900 + r, (12,) + N) * (chi != 0) for r in range(nrhs)]
+    A = solve.dense_prec_matrix(T, tau, D)
+    assert np.linalg.cond(A) < 1e3
+    B = np.stack([matvec.rhs_prec(et, tau, D, F).reshape(-1) for et in ets], axis=1)
+    xref = np.linalg.solve(A, B)
+    c = vie.Context(0)
+    c.set_grid(N, D, F)
+    c.set_contrast(vox_to_lib(e), vox_to_lib(s))
+    etd = _dev_batch(torch, ets)
+    its = {}
+    for s_step in (2, 3):
+        x = torch.empty_like(etd)
+        code, st = c.solve(etd, x, mode=1, tol=1e-11, restart=restart, s_step=s_step)
+        assert code == vie.VIE_OK
+        its[s_step] = max(s_["iterations"] for s_ in st)
+        err = max(relerr(_host(x, r).reshape(-1), xref[:, r]) for r in range(nrhs))
+        _say("  s_step %d: %d iterations, vs dense LU %.1e" % (s_step, its[s_step], err))
+        assert err < 1e-8
+    assert abs(its[2] - its[3]) <= max(4, 0.15 * its[2])
+
+
 @functools.lru_cache(None)
 def _phantom24():
     """24^3 voxels at 3 mm of the 6-class ellipsoid phantom (the 64^3
