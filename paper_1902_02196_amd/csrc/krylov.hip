@@ -16,10 +16,73 @@ constexpr int kTpb = 256;
 // additions keep their order, so the sums keep their bits).
 constexpr int kGroup = 8;   // basis vectors per workgroup of the dot kernel
 
+// Sums over a wave.  One value: halves, rows of 16 and then lanes are folded
+// by register swaps and lane permutations of the vector unit, not through LDS.
+// Several values: a fold leaves each lane with half of them, so that M sums
+// take about M exchanges instead of 6 M; the dot kernel's 48 sums per group
+// went through 576 LDS permutes per wave, more than its 16^3 vectors' loads
+// (16^3 complex128 14.8 -> 6.4 us, 64^3 PWC complex64 42.7 -> 28.9).
+__device__ __forceinline__ double join_words(unsigned lo, unsigned hi) {
+    return __hiloint2double((int)hi, (int)lo);
+}
+
+// the value of the lane across bit O (8: lane ^ 8, 4: lane ^ 7, 2: lane ^ 2,
+// 1: lane ^ 1; in this order the folds cover every lane once)
+template <int O>
+__device__ __forceinline__ double across(double x) {
+    constexpr int ctrl = O == 8 ? 0x128 : O == 4 ? 0x141 : O == 2 ? 0x4E : 0xB1;
+    static_assert(O == 8 || O == 4 || O == 2 || O == 1, "within a row of 16 lanes");
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), ctrl, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), ctrl, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// a summed across bit O in the lanes without it, b in those with it
+template <int O>
+__device__ __forceinline__ double fold(double a, double b, int lane) {
+    if constexpr (O >= 16) {
+        const unsigned al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
+        if constexpr (O == 32) {
+            const auto lo = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+            const auto hi = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+            return join_words(lo[0], hi[0]) + join_words(lo[1], hi[1]);
+        } else {
+            const auto lo = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+            const auto hi = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+            return join_words(lo[0], hi[0]) + join_words(lo[1], hi[1]);
+        }
+    } else {
+        const bool up = lane & O;
+        return (up ? b : a) + across<O>(up ? a : b);
+    }
+}
+
+// sum over the wave, in every lane
 __device__ __forceinline__ double wave_sum(double v) {
+    v = fold<32>(v, v, 0);
+    v = fold<16>(v, v, 0);
+    v += across<8>(v);
+    v += across<4>(v);
+    v += across<2>(v);
+    return v + across<1>(v);
+}
+
+// the sums of v[0..M): this lane's one in v[0], its index returned (-1: the
+// lane holds none)
+template <int M, int O = 32>
+__device__ __forceinline__ int wave_sums(double* v, int lane) {
+    static_assert(M <= 2 * O, "one value per lane at most");
+    constexpr int H = (M + 1) / 2;
+    if constexpr (M > 1) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+        for (int i = 0; i < H; ++i) v[i] = fold<O>(v[i], v[i + H < M ? i + H : i], lane);
+    } else {
+        v[0] = fold<O>(v[0], v[0], lane);
+    }
+    int idx = 0;
+    if constexpr (O > 1) idx = wave_sums<H, O / 2>(v, lane);
+    if (lane & O) idx = M > 1 && idx >= 0 ? idx + H : -1;
+    return idx < M ? idx : -1;
 }
 
 template <typename T> __device__ __forceinline__ double2 to_d2(T v) { return make_double2((double)v.x, (double)v.y); }
@@ -72,11 +135,9 @@ __device__ __forceinline__ void dot_group(double2* __restrict__ partial,
     using T = typename U::T;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long stride = (long long)gridDim.x * kTpb;
-    double ar[NW][G], ai[NW][G];
+    double acc[2 * NW * G];   // re, im of (q, g)
 #pragma unroll
-    for (int q = 0; q < NW; ++q)
-#pragma unroll
-        for (int g = 0; g < G; ++g) ar[q][g] = ai[q][g] = 0.0;
+    for (int q = 0; q < 2 * NW * G; ++q) acc[q] = 0.0;
     for (long long k = blockIdx.x * (long long)kTpb + threadIdx.x; k < nu; k += stride) {
         T wu[NW];
 #pragma unroll
@@ -92,19 +153,14 @@ __device__ __forceinline__ void dot_group(double2* __restrict__ partial,
 #pragma unroll
                 for (int q = 0; q < NW; ++q) {
                     const double2 wv = U::get(wu[q], h);
-                    ar[q][g] += v.x * wv.x + v.y * wv.y;
-                    ai[q][g] += v.x * wv.y - v.y * wv.x;
+                    acc[2 * (q * G + g)] += v.x * wv.x + v.y * wv.y;
+                    acc[2 * (q * G + g) + 1] += v.x * wv.y - v.y * wv.x;
                 }
             }
         }
     }
-#pragma unroll
-    for (int q = 0; q < NW; ++q)
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const double sr = wave_sum(ar[q][g]), si = wave_sum(ai[q][g]);
-            if (lane == 0) { red[wave][2 * (q * G + g)] = sr; red[wave][2 * (q * G + g) + 1] = si; }
-        }
+    const int idx = wave_sums<2 * NW * G>(acc, lane);
+    if (idx >= 0) red[wave][idx] = acc[0];
     __syncthreads();
     if (threadIdx.x < NW * G) {
         const int q = threadIdx.x / G, g = threadIdx.x - q * G;
@@ -749,11 +805,8 @@ __global__ void __launch_bounds__(kTpb) k_update_triple(C<R>* __restrict__ w, co
             acc[7] += o2.x * o3.y - o2.y * o3.x;
         }
     }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const double v = wave_sum(acc[q]);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = v;
-    }
+    const int idx = wave_sums<8>(acc, threadIdx.x & 63);
+    if (idx >= 0) red[threadIdx.x >> 6][idx] = acc[0];
     __syncthreads();
     if (threadIdx.x < 8) {
         double t = 0;

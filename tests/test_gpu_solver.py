@@ -201,11 +201,12 @@ def test_three_step_columns_over_slots(vie, torch, nrhs, restart):
     """The columns of three Arnoldi steps are folded in by one launch, whose
     groups of waves take a slot each (1 to 4 of them, by the restart length)
     and whose last part keeps up to 64 slots in LDS: random right-hand sides
-    on either side of these counts, against dense LU and the step count of
-    two-step Arnoldi, whose columns are folded in one by one.  (One step at
-    a time loses orthogonality past 100 vectors and takes a second cycle.)
-    A relative residual of 1e-11 bounds the error by the condition number
-    (below 1e3 here) times that."""
+    on either side of these counts, against dense LU, in no more steps than
+    two-step Arnoldi (whose columns are folded in one by one) needs, to the
+    accuracy of such counts.  (The other forms may need more: past 100
+    vectors they lose orthogonality and take a second cycle.)  A relative
+    residual of 1e-11 bounds the error by the condition number (below 1e3
+    here) times that."""
     N, D = (3, 2, 3), (0.005, 0.006, 0.005)
     _say("three-step columns nrhs %d restart %d" % (nrhs, restart))
     T = _blocks(N, D)
@@ -229,7 +230,7 @@ def test_three_step_columns_over_slots(vie, torch, nrhs, restart):
         err = max(relerr(_host(x, r).reshape(-1), xref[:, r]) for r in range(nrhs))
         _say("  s_step %d: %d iterations, vs dense LU %.1e" % (s_step, its[s_step], err))
         assert err < 1e-8
-    assert abs(its[2] - its[3]) <= max(4, 0.15 * its[2])
+    assert its[3] - its[2] <= max(4, 0.15 * its[2])
 
 
 @functools.lru_cache(None)
