@@ -180,7 +180,9 @@ struct ArnoldiState {
     double2* g;            // [na][m + 1]
     const double2* slot;   // [na]: (||r||, target of |g_{j+1}| / ||r||)
     int* status;           // [0] columns folded in, [1] every slot has met its
-                           // target, [2] a non-finite estimate was seen
+                           // target, [2] a non-finite estimate was seen, [3]
+                           // largest estimate of an open slot over its target
+                           // (bits of a float)
     int m;
     double2* Hr;           // [na][m][m + 1]: the unrotated columns (or nullptr)
 };

@@ -1076,11 +1076,13 @@ __global__ void __launch_bounds__(64 * kGivWaves) k_givens(ArnoldiState st, cons
     __shared__ double2 lh[kGivWaves][kGivRows], lc[kGivWaves][kGivRows], ls[kGivWaves][kGivRows];
     __shared__ double lhn[kGivWaves];
     __shared__ int open, bad;
+    __shared__ unsigned left;
     const bool stopped = st.status[1] | st.status[2];   // uniform: stopped at an earlier column
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, m = st.m, nvec = j + 1;
     if (threadIdx.x == 0) {
         open = 0;
         bad = 0;
+        left = 0;
     }
     for (int base = 0; base < na; base += kGivWaves) {   // the same trip count in every wave
         const int s = base + wv;
@@ -1142,7 +1144,10 @@ __global__ void __launch_bounds__(64 * kGivWaves) k_givens(ArnoldiState st, cons
             g[j] = cmul(c, gj);
             const double est = sqrt(gn.x * gn.x + gn.y * gn.y) / st.slot[s].x;
             if (!isfinite(est)) atomicOr(&bad, 1);
-            if (!(est <= st.slot[s].y) && hn > 0.0) atomicOr(&open, 1);
+            if (!(est <= st.slot[s].y) && hn > 0.0) {
+                atomicOr(&open, 1);
+                atomicMax(&left, __float_as_uint((float)(est / st.slot[s].y)));
+            }
         }
         __syncthreads();   // the LDS rows are reused by the next round
     }
@@ -1150,6 +1155,7 @@ __global__ void __launch_bounds__(64 * kGivWaves) k_givens(ArnoldiState st, cons
         st.status[0] = nvec;
         if (bad) st.status[2] = 1;
         if (!open) st.status[1] = 1;
+        st.status[3] = (int)left;
     }
 }
 
@@ -1307,6 +1313,7 @@ __global__ void __launch_bounds__(64 * kColWaves * 4) k_triple_finish(
     if (stopped || threadIdx.x >= 64) return;
     for (int q = 0; q < 3; ++q) {   // column j + q of every slot, a lane each
         bool open = false, bad = false;
+        float left = 0.0f;
         for (int s = lane; s < na; s += 64) {
             double2* tl = tail + kTripleTail * s;
             const double2 a = tl[q == 0 ? 0 : q == 1 ? 1 : 3];
@@ -1344,13 +1351,19 @@ __global__ void __launch_bounds__(64 * kColWaves * 4) k_triple_finish(
             tl[8] = gn;
             const double est = sqrt(gn.x * gn.x + gn.y * gn.y) / sl.x;
             if (!isfinite(est)) bad = true;
-            if (!(est <= sl.y) && hn > 0.0) open = true;
+            if (!(est <= sl.y) && hn > 0.0) {
+                open = true;
+                left = fmaxf(left, (float)(est / sl.y));
+            }
         }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) left = fmaxf(left, __shfl_xor(left, o, 64));
         const bool any_open = __any(open), any_bad = __any(bad);
         if (lane == 0) {
             st.status[0] = j + q + 1;
             if (any_bad) st.status[2] = 1;
             if (!any_open) st.status[1] = 1;
+            st.status[3] = __float_as_int(left);
         }
         if (any_bad || !any_open) break;
     }
