@@ -61,6 +61,8 @@ bool p3_jm_supported(int es, int n);   // either J-M x pass
 // x pass of the PWC basis (3 component rows per pencil, compiled lengths only)
 template <typename R>
 void launch_p3_pwc(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s);
+template <typename R, int N>   // all siblings of an octant row in one workgroup, N = 256
+void launch_p3_pwc_rows(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s);
 // x pass of the curl operator K (U the [Oz][Oy][30][Ox] octant)
 template <typename R>
 void launch_p3_curl(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s);
@@ -71,6 +73,8 @@ void launch_p3_curl(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, h
 template <typename R>
 bool launch_p3_jm(C<R>* A, const C<R>* UN, const C<R>* UK, const P3Params& p, const C<R>* tw, C<R> kj, C<R> km,
                   hipStream_t s);
+// x-pass lengths of the kernels in passes.hip and of the PWC pass
+#define VIE_P3_LENGTHS(X) X(8) X(16) X(32) X(64) X(96) X(128) X(160) X(192) X(256) X(320) X(384) X(512)
 bool p3_ct_supported(int n);
 int p3_ct_groups(int es, int n);
 bool p3_ct_fits(int es, int n);

@@ -1100,9 +1100,6 @@ __global__ void __launch_bounds__(kP3PwcThreads) k_p3_pwc(C<R>* __restrict__ A, 
     lds_to_rows<R, N, NT>(buf, nrows, p.Nx, rowp);
 }
 
-// lengths with a compile-time kernel
-#define VIE_P3_LENGTHS(X) X(8) X(16) X(32) X(64) X(96) X(128) X(160) X(192) X(256) X(320) X(384) X(512)
-
 bool p3_ct_supported(int n) {
     switch (n) {
 #define CASE(n_) case n_:
@@ -1161,7 +1158,7 @@ static void launch_p3_quad_n(C<R>* A, const C<R>* U, const P3Params& p, const C<
 }
 
 template <typename R, int N>
-static void launch_p3_pwc_n(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s) {
+void launch_p3_pwc_rows(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s) {
     const size_t lds = ((size_t)N + lds_pad(12 * N) + 2) * sizeof(C<R>);
     const long long rows8 = ((long long)p.Oy * p.Oz + 7) / 8 * 8;
     const long long nblk = rows8 * p.nrhs;
@@ -1360,29 +1357,14 @@ template bool launch_p3_jm<float>(C<float>*, const C<float>*, const C<float>*, c
 template bool launch_p3_jm<double>(C<double>*, const C<double>*, const C<double>*, const P3Params&,
                                    const C<double>*, C<double>, C<double>, hipStream_t);
 
-template <typename R>
-void launch_p3_pwc(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s) {
-    VIE_REQUIRE(2 * p.Nx <= p.plan.n, -1, "x pass: fft length below 2 Nx");
-    switch (p.plan.n) {
-#define CASE(n_)                                        \
-    case n_:                                           \
-        launch_p3_pwc_n<R, n_>(A, U, p, tw, s);        \
-        return;
-        VIE_P3_LENGTHS(CASE)
-#undef CASE
-        default: break;
-    }
-    throw Error(-1, "the PWC x pass needs an fft length along x of 8, 16, 32, 64, 96, 128, 160, 192, 256, "
-                            "320, 384 or 512");
-}
-
+template void launch_p3_pwc_rows<float, 256>(C<float>*, const C<float>*, const P3Params&, const C<float>*, hipStream_t);
+template void launch_p3_pwc_rows<double, 256>(C<double>*, const C<double>*, const P3Params&, const C<double>*,
+                                              hipStream_t);
 template void launch_strided<float>(bool, const C<float>*, C<float>*, const StridedPass&, long long, long long,
                                     const C<float>*, const Epilogue<float>*, hipStream_t);
 template void launch_strided<double>(bool, const C<double>*, C<double>*, const StridedPass&, long long, long long,
                                      const C<double>*, const Epilogue<double>*, hipStream_t);
 template void launch_p3<float>(C<float>*, const C<float>*, const P3Params&, const C<float>*, hipStream_t);
 template void launch_p3<double>(C<double>*, const C<double>*, const P3Params&, const C<double>*, hipStream_t);
-template void launch_p3_pwc<float>(C<float>*, const C<float>*, const P3Params&, const C<float>*, hipStream_t);
-template void launch_p3_pwc<double>(C<double>*, const C<double>*, const P3Params&, const C<double>*, hipStream_t);
 
 }  // namespace vie

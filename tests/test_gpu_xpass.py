@@ -128,6 +128,31 @@ def test_every_length(vie, torch, M):
             assert err < 50 * eps, (N, dtype, err)
 
 
+@pytest.mark.parametrize("M", [8, 16, 32, 64, 96, 128, 160, 192, 256, 320, 384, 512])
+def test_pwc_every_length(vie, torch, M):
+    """The PWC product (the pulse functions alone, a = 4 p) at every length it
+    takes: ragged rows, single and paired siblings in y and z, two right-hand
+    sides, both precisions."""
+    for N in ((M // 2, 3, 2), (max(1, M // 2 - 3), 2, 3)):
+        c = vie.Context(0)
+        c.set_grid(N, (0.003, 0.004, 0.005), F, fft_size=(M, 2 * N[1], 2 * N[2]))
+        Th = c.get_toeplitz()
+        T = torch.from_numpy(Th).cuda()
+        c.set_basis(3)
+        c.set_toeplitz(Th)
+        x = _random(torch, torch.Generator(device="cuda").manual_seed(M + 1), c.vec_shape(2))
+        for dtype, eps in ((torch.complex64, 6e-8), (torch.complex128, 1.2e-16)):
+            print("M %d N %s %s" % (M, N, dtype), flush=True)
+            xd = x.to(dtype).contiguous()
+            y = torch.full_like(xd, float("nan"))
+            c.apply(xd, y, op=vie.OP_N)
+            x12 = torch.zeros((2, 12) + tuple(xd.shape[2:]), dtype=torch.complex128, device="cuda")
+            x12[:, ::4] = xd
+            r = reference(torch, T, x12)[:, ::4]
+            err = ((y.to(torch.complex128) - r).norm() / r.norm()).item()
+            assert err < 50 * eps, (N, dtype, err)
+
+
 def _random(torch, g, shape):
     return torch.view_as_complex(torch.randn(tuple(shape) + (2,), generator=g, device="cuda", dtype=torch.float64))
 
