@@ -372,16 +372,102 @@ FarTables build_far_tables(const AssemblyTables& T) {
     return F;
 }
 
-// One workgroup of W wavefronts per offset (grid-stride over the offsets of
-// the cube that holds the band, those below the band skipped); wavefront w
-// takes the x abscissae w, w + W, ...  Per x abscissa: the (y, z) slab of
-// Green's values, the z contraction for all 16 kernel pairs, the y
+// Weights and points of one lane, fixed for the launch: of its z kernel (tid %
+// 16), of its (ky, kz) pair, and the points (y, z) of a slab it evaluates
+// with how many of the two are point values (2 bits each).
+template <int P>
+struct FarLane {
+    static constexpr int RG = (P * P + 63) / 64;
+    static_assert(RG <= 16, "flags of a lane in 32 bits");
+    double wz[P], wy[P], gy[RG], gz[RG], ryz[RG];
+    unsigned npt = 0;
+    int tid, kzp;
+
+    __device__ __forceinline__ FarLane(const FarTables& F, const FarBand& B, int lane) : tid(lane) {
+        const int kz = tid & 15, p = min(tid, F.npair - 1), ky = F.pair_ky[p];
+        kzp = F.pair_kz[p];
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            wz[k] = B.W[2][kz][k];
+            wy[k] = B.W[1][ky][k];
+        }
+#pragma unroll
+        for (int u = 0; u < RG; ++u) {
+            const int idx = min(tid + 64 * u, P * P - 1), j = idx / P, k = idx - j * P;
+            gy[u] = B.w[1][j];
+            gz[u] = B.w[2][k];
+            npt |= (unsigned)(B.ispt[j] + B.ispt[k]) << (2 * u);
+        }
+    }
+    // squared distances in y and z at offset (y0, z0)
+    __device__ __forceinline__ void place(double y0, double z0) {
+#pragma unroll
+        for (int u = 0; u < RG; ++u) {
+            const double ry = y0 + gy[u], rz = z0 + gz[u];
+            ryz[u] = ry * ry + rz * rz;
+        }
+    }
+    // the (y, z) slab of Green's values at x distance rx; pi: 1 at a point value of x
+    __device__ __forceinline__ void slab(double2* g, double rx, int pi, double k0) const {
+#pragma unroll
+        for (int u = 0; u < RG; ++u) {
+            const int idx = tid + 64 * u;
+            if (idx < P * P)
+                g[idx] = pi + (int)((npt >> (2 * u)) & 3) <= 1 ? green(sqrt(rx * rx + ryz[u]), k0)
+                                                                : make_double2(0, 0);
+        }
+    }
+    // z contraction of a slab for the 16 kernels
+    __device__ __forceinline__ void contract_z(double2* t1, const double2* g) const {
+        for (int idx = tid; idx < P * 16; idx += 64) {
+            const int j = idx >> 4;   // kernel idx % 16 = tid % 16
+            double2 a = make_double2(0, 0);
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const double2 v = g[j * P + k];
+                a.x += wz[k] * v.x;
+                a.y += wz[k] * v.y;
+            }
+            t1[idx] = a;
+        }
+    }
+    // y contraction for the (ky, kz) pairs in use
+    __device__ __forceinline__ void contract_y(double2* t2, const double2* t1, const FarTables& F,
+                                               const FarBand& B) const {
+        if (tid < F.npair) {
+            double2 a = make_double2(0, 0);
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const double2 u = t1[j * 16 + kzp];
+                a.x += wy[j] * u.x;
+                a.y += wy[j] * u.y;
+            }
+            t2[tid] = a;
+        }
+        for (int p = tid + 64; p < F.npair; p += 64) {
+            const double* w2 = B.W[1][F.pair_ky[p]];
+            const int kz = F.pair_kz[p];
+            double2 a = make_double2(0, 0);
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const double2 u = t1[j * 16 + kz];
+                a.x += w2[j] * u.x;
+                a.y += w2[j] * u.y;
+            }
+            t2[p] = a;
+        }
+    }
+};
+
+// Near bands: one workgroup of W wavefronts per offset (grid-stride over the
+// offsets of the cube that holds the band, those below the band skipped);
+// wavefront w takes the x abscissae w, w + W, ...  Per x abscissa: the (y, z)
+// slab of Green's values, the z contraction for all 16 kernel pairs, the y
 // contraction for the (ky, kz) pairs in use, and the x accumulation of every
 // (entry, term) sum; the wavefronts' sums are added in order at the end.
-// W = 4 for the near bands, whose 19, 98 and 604 offsets leave most of the
-// chip idle and wait on one wavefront's serial chain (270, 76 and 74 us;
-// with W = 1 576, 326 and 199 us); the far bands have thousands of offsets
-// and take W = 1.
+// W = 4: 19, 98 and 604 offsets leave most of the chip idle and wait on one
+// wavefront's serial chain (214, 80 and 46 us; one wavefront each 576,
+// 326 and 199).
 template <int P, int W>
 __global__ void __launch_bounds__(64 * W) k_assemble_far(double2* __restrict__ out, const FarTables* __restrict__ Fg,
                                                          int b, double Dx, double Dy, double Dz, double k0, int Nx,
@@ -396,7 +482,8 @@ __global__ void __launch_bounds__(64 * W) k_assemble_far(double2* __restrict__ o
     double2* t1 = t1_[w];
     double2* t2 = t2_[w];
     const long long V = (long long)Nx * Ny * Nz;
-    const int nterm = F.nterm, npair = F.npair;
+    const int nterm = F.nterm;
+    FarLane<P> lane(F, B, tid);
     // offsets of the band lie in the cube [0, cx) x [0, cy) x [0, cz)
     const long long ncube = (long long)cx * cy * cz;
     for (long long q = blockIdx.x; q < ncube; q += gridDim.x) {
@@ -404,53 +491,18 @@ __global__ void __launch_bounds__(64 * W) k_assemble_far(double2* __restrict__ o
         const long long v = ((long long)d2 * Ny + d1) * Nx + d0;
         const int dinf = max(d0, max(d1, d2));
         if (dinf < B.dlo || dinf > B.dhi) continue;   // uniform over the workgroup
+        lane.place(d1 * Dy, d2 * Dz);
         double2 s0 = make_double2(0, 0), s1 = make_double2(0, 0);   // terms tid, tid + 64
         // every wavefront runs every round (barriers); one past the last
         // abscissa has nothing to add
         for (int i0 = 0; i0 < P; i0 += W) {
             const int i = i0 + w;
             const bool act = i < P;
-            if (act) {
-                const double rx = d0 * Dx + B.w[0][i];
-                const int pi = B.ispt[i];
-                for (int idx = tid; idx < P * P; idx += 64) {
-                    const int j = idx / P, k = idx - j * P;
-                    double2 g = make_double2(0, 0);
-                    if (pi + B.ispt[j] + B.ispt[k] <= 1) {
-                        const double ry = d1 * Dy + B.w[1][j], rz = d2 * Dz + B.w[2][k];
-                        g = green(sqrt(rx * rx + ry * ry + rz * rz), k0);
-                    }
-                    slab[idx] = g;
-                }
-            }
+            if (act) lane.slab(slab, d0 * Dx + B.w[0][i], B.ispt[i], k0);
             __syncthreads();
-            if (act)
-                for (int idx = tid; idx < P * 16; idx += 64) {
-                    const int j = idx >> 4, kz = idx & 15;
-                    const double* wz = B.W[2][kz];
-                    double2 a = make_double2(0, 0);
-#pragma unroll
-                    for (int k = 0; k < P; ++k) {
-                        const double2 g = slab[j * P + k];
-                        a.x += wz[k] * g.x;
-                        a.y += wz[k] * g.y;
-                    }
-                    t1[idx] = a;
-                }
+            if (act) lane.contract_z(t1, slab);
             __syncthreads();
-            if (act)
-                for (int p = tid; p < npair; p += 64) {
-                    const double* wy = B.W[1][F.pair_ky[p]];
-                    const int kz = F.pair_kz[p];
-                    double2 a = make_double2(0, 0);
-#pragma unroll
-                    for (int j = 0; j < P; ++j) {
-                        const double2 u = t1[j * 16 + kz];
-                        a.x += wy[j] * u.x;
-                        a.y += wy[j] * u.y;
-                    }
-                    t2[p] = a;
-                }
+            if (act) lane.contract_y(t2, t1, F, B);
             __syncthreads();
             if (act && tid < nterm) {
                 const double wx = B.W[0][F.term_kx[tid]][i];
@@ -480,6 +532,105 @@ __global__ void __launch_bounds__(64 * W) k_assemble_far(double2* __restrict__ o
             out[(long long)tid * V + v] = a;
         }
         __syncthreads();
+    }
+}
+
+// Far bands: one wavefront per run of up to T offsets along x.  Neighbouring
+// offsets share their x abscissae, the Gauss points of the cell between two of
+// them and the lattice points, so each plane x = const is evaluated and
+// contracted in y and z once and added to the two (cell) or three (lattice)
+// offsets it belongs to: n + 1 planes per offset of a long run instead of
+// 2 n + 3.  Bound by the FP64 Green's function (sqrt, sincos, division) of a
+// plane's points: 1.39 ms at 48^3 with all planes per offset and the weights
+// reloaded each time, 1.06 with the weights in registers, 0.59 so (64^3: 2.6 ->
+// 1.35).
+template <int P>
+__global__ void __launch_bounds__(64) k_assemble_far_rows(double2* __restrict__ out,
+                                                          const FarTables* __restrict__ Fg, int b, double Dx,
+                                                          double Dy, double Dz, double k0, int Nx, int Ny, int Nz,
+                                                          int cx, int cy, int cz, int T) {
+    constexpr int n = (P - 3) / 2;
+    __shared__ double2 slab[P * P];
+    __shared__ double2 t1[P * 16];
+    __shared__ double2 t2[kFarTerms];
+    __shared__ double wx[16 * P];
+    const FarTables& F = *Fg;
+    const FarBand& B = F.band[b];
+    const int tid = threadIdx.x;
+    const long long V = (long long)Nx * Ny * Nz;
+    const int nterm = F.nterm;
+    FarLane<P> lane(F, B, tid);
+    for (int idx = tid; idx < 16 * P; idx += 64) wx[idx] = B.W[0][idx / P][idx % P];
+    const double* wt[2];
+    int pr[2];
+    bool has[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {   // terms tid, tid + 64
+        const int t = min(tid + 64 * h, nterm - 1);
+        has[h] = tid + 64 * h < nterm;
+        wt[h] = wx + F.term_kx[t] * P;
+        pr[h] = F.term_pair[t];
+    }
+    const int nch = (cx + T - 1) / T;
+    const long long nrun = (long long)nch * cy * cz;
+    for (long long q = blockIdx.x; q < nrun; q += gridDim.x) {
+        const int ch = int(q % nch), d1 = int((q / nch) % cy), d2 = int(q / ((long long)nch * cy));
+        // the band's offsets of a row: all of it, or those from dlo on
+        const int x0 = (max(d1, d2) >= B.dlo ? 0 : B.dlo) + ch * T, x1 = min(x0 + T, cx);
+        if (x0 >= x1) continue;   // uniform over the workgroup
+        lane.place(d1 * Dy, d2 * Dz);
+        double2 s[3][2];   // sums of the offsets c - 1, c, c + 1
+#pragma unroll
+        for (int k = 0; k < 3; ++k) s[k][0] = s[k][1] = make_double2(0, 0);
+        for (int c = x0 - 1; c <= x1; ++c) {
+            // the lattice plane x = c, then the Gauss planes of the cell [c, c + 1]
+            for (int a = -1; a < (c < x1 ? n : 0); ++a) {
+                lane.slab(slab, c * Dx + (a < 0 ? 0.0 : B.w[0][n + a]), a < 0, k0);
+                __syncthreads();
+                lane.contract_z(t1, slab);
+                __syncthreads();
+                lane.contract_y(t2, t1, F, B);
+                __syncthreads();
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const double2 u = t2[pr[h]];
+                    auto add = [&](double2& acc, double w) {
+                        acc.x += w * u.x;
+                        acc.y += w * u.y;
+                    };
+                    if (a < 0) {
+                        add(s[0][h], wt[h][2 * n + 2]);
+                        add(s[1][h], wt[h][2 * n + 1]);
+                        add(s[2][h], wt[h][2 * n]);
+                    } else {
+                        add(s[1][h], wt[h][n + a]);
+                        add(s[2][h], wt[h][a]);
+                    }
+                }
+                __syncthreads();
+                if (a < 0 && c > x0) {   // offset c - 1 is complete: combine the terms of each entry
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        if (has[h]) t2[tid + 64 * h] = s[0][h];
+                    __syncthreads();
+                    if (tid < F.nent) {
+                        double2 r = make_double2(0, 0);
+                        for (int t = F.ent_first[tid]; t < F.ent_first[tid] + F.ent_count[tid]; ++t) {
+                            r.x += F.term_coef[t] * t2[t].x;
+                            r.y += F.term_coef[t] * t2[t].y;
+                        }
+                        out[(long long)tid * V + ((long long)d2 * Ny + d1) * Nx + (c - 1)] = r;
+                    }
+                    __syncthreads();
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                s[0][h] = s[1][h];
+                s[1][h] = s[2][h];
+                s[2][h] = make_double2(0, 0);
+            }
+        }
     }
 }
 
@@ -641,15 +792,25 @@ void assemble_blocks(double2* out, const AssemblyTables& T, int Nx, int Ny, int 
         hipLaunchKernelGGL((k_assemble_far<P_, W_>), dim3(grid), dim3(64 * W_), 0, s, out, dF, b, D[0], D[1],    \
                            D[2], T.k0, Nx, Ny, Nz, cx, cy, cz);                                                  \
         break;
+        // runs as long as leaves 8192 of them (12 wavefronts per CU fill the
+        // chip with 3072), at most 16
+        const int run = (int)std::max<long long>(1, std::min<long long>(cnt / 8192, 16));
+        const long long runs = (long long)((cx + run - 1) / run) * cy * cz;
+#define FAR_ROWS(P_)                                                                                             \
+    case P_:                                                                                                     \
+        hipLaunchKernelGGL(k_assemble_far_rows<P_>, dim3((unsigned)std::min<long long>(runs, 1 << 16)), dim3(64), \
+                           0, s, out, dF, b, D[0], D[1], D[2], T.k0, Nx, Ny, Nz, cx, cy, cz, run);               \
+        break;
         switch (B.P) {
             FAR_CASE(31, 4)
             FAR_CASE(21, 4)
             FAR_CASE(17, 4)
-            FAR_CASE(13, 1)
-            FAR_CASE(11, 1)
+            FAR_ROWS(13)
+            FAR_ROWS(11)
             default: throw Error(-1, "assembly: unsupported Gauss order band");
         }
 #undef FAR_CASE
+#undef FAR_ROWS
         VIE_HIP(hipGetLastError());
     }
     VIE_HIP(hipStreamSynchronize(s));

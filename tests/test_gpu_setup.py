@@ -46,6 +46,25 @@ def test_assembly_on_degenerate_grids(vie, N, D):
                 assert np.abs(a - b).max() <= 1e-10 * np.abs(b).max(), (ix, iy, iz)
 
 
+@pytest.mark.parametrize("N", [(60, 24, 20), (50, 64, 48), (19, 120, 70), (18, 30, 40)])
+def test_far_offsets_do_not_depend_on_the_run(vie, N):
+    """The tensors of an offset depend on it alone; in a large grid the far
+    offsets are evaluated in runs along x (of 2 to 16, with remainders, from
+    the row's start or from where the band begins), in a grid of one plane
+    one by one.  The sums are the same up to their order: 1e3 terms in FP64,
+    1e-12 of the largest entry."""
+    D = (0.003, 0.004, 0.005)
+    print("far runs %s" % (N,), flush=True)
+    c = vie.Context(0)
+    c.set_grid(N, D, F)
+    big = c.get_toeplitz()
+    for n, part in (((N[0], N[1], 1), big[:, :1]), ((N[0], 1, N[2]), big[:, :, :1])):
+        c.set_grid(n, D, F)
+        ref = c.get_toeplitz()
+        assert np.isfinite(part).all()
+        assert (np.abs(part - ref).max(axis=0) <= 1e-12 * np.abs(ref).max(axis=0)).all(), n
+
+
 def test_setup_beside_captured_solves(vie):
     """Graph captures of one thread's solves and the grid set-ups of another
     do not disturb each other: every call succeeds, every solution has the
