@@ -45,6 +45,11 @@ def block_flops(M, nrhs, nc=12):
 
 # sources whose change invalidates counter measurements of the kernels
 KERNEL_SOURCES = ["paper_1902_02196_amd/csrc/passes.hip", "paper_1902_02196_amd/csrc/strided.hip",
+                  "paper_1902_02196_amd/csrc/xpass.hpp", "paper_1902_02196_amd/csrc/xpass_f32.hip",
+                  "paper_1902_02196_amd/csrc/xpass_f64.hip", "paper_1902_02196_amd/csrc/xpass_pwc.hip",
+                  "paper_1902_02196_amd/csrc/xpass_jm.hip", "paper_1902_02196_amd/csrc/xpass_curl.hip",
+                  "paper_1902_02196_amd/csrc/strided_mix.hpp", "paper_1902_02196_amd/csrc/strided_mix_f32.hip",
+                  "paper_1902_02196_amd/csrc/strided_mix_f64.hip", "paper_1902_02196_amd/csrc/fft_mix.hpp",
                   "paper_1902_02196_amd/csrc/fft.hpp", "paper_1902_02196_amd/csrc/fft_ct.hpp",
                   "paper_1902_02196_amd/csrc/passes.hpp", "paper_1902_02196_amd/csrc/common.hpp",
                   "paper_1902_02196_amd/csrc/krylov.hip", "paper_1902_02196_amd/csrc/apply.cpp"]
