@@ -142,17 +142,19 @@ int strided_tile_for(int es, int n) {
 }
 
 // Which kernel runs: the fft_mix.hpp lengths have theirs (strided_mix.hpp),
-// faster than this file's everywhere but in the epilogue pass at 128, 160 and
-// 192 in complex64 (P^-1 A at 64^3: 27.9 us here against 29.7, 80^3 x 2: 114
-// against 134, 96^3: 107 against 119).  768 is this file's alone.
+// as fast as this file's or faster (epilogue pass of P^-1 A in complex64: 64^3
+// 28.3 us here against 28.6, 96^3 108 against 100, 40 x 36 x 64 13.1 against
+// 10.9, PWC 64^3 10.5 against 9.2) but for the epilogue pass at 160 in
+// complex64 (80^3, two vectors: 112 us here against 121, J-M 68 against 91).
+// 768 is this file's alone.
 template <typename R, bool FWD, bool EPI>
 static bool launch_strided_ct(const C<R>* in, C<R>* out, const StridedPass& p, long long n_o2, long long n_o1,
                               const C<R>* tw, const Epilogue<R>& ep, hipStream_t s) {
     if constexpr (EPI && sizeof(R) == 4) {
-        if (p.plan.n == 128) launch_strided_ct_nt<R, FWD, EPI, 128, 16>(in, out, p, n_o2, n_o1, tw, ep, s);
-        if (p.plan.n == 160) launch_strided_ct_nt<R, FWD, EPI, 160, 16>(in, out, p, n_o2, n_o1, tw, ep, s);
-        if (p.plan.n == 192) launch_strided_ct_nt<R, FWD, EPI, 192, 16>(in, out, p, n_o2, n_o1, tw, ep, s);
-        if (p.plan.n == 128 || p.plan.n == 160 || p.plan.n == 192) return true;
+        if (p.plan.n == 160) {
+            launch_strided_ct_nt<R, FWD, EPI, 160, 16>(in, out, p, n_o2, n_o1, tw, ep, s);
+            return true;
+        }
     }
     if (p.plan.n != 768) return launch_strided_mix<R>(FWD, EPI, in, out, p, n_o2, n_o1, tw, ep, s);
     if (!strided_ct_fits((int)sizeof(C<R>), 768, p.tile)) return false;
