@@ -242,10 +242,10 @@ void launch_update_triple(C<R>* w, const C<R>* Vb, long long ldv, int nvec, cons
                           const double2* g, long long n, long long rstride_v, long long rstride_w,
                           double* norm_partial, double* gram_partial, const double* ivn, long long ivn_ld, int jw,
                           int nrhs, int nblocks, hipStream_t s);
-void launch_triple_coef(double2* tc, const double* gpart, int nblocks, int nrhs, hipStream_t s);
+// forms the block's coefficients tc from gpart (nblocks workgroups) as well
 template <typename R>
-void launch_axpy_triple(C<R>* u1, long long ldv, long long n, long long rstride, const double2* tc, double* np2,
-                        double* np3, int nrhs, int nblocks, hipStream_t s);
+void launch_axpy_triple(C<R>* u1, long long ldv, long long n, long long rstride, double2* tc, const double* gpart,
+                        double* np2, double* np3, int nrhs, int nblocks, hipStream_t s);
 // columns j .. j + 2 of a triple folded into the rotations (np1..3: norm
 // partials of u_{j+1..j+3}, their reciprocal norms to ivn[s * ivn_ld + 0..2]),
 // the stop flags as after three launch_givens; tail: scratch [na][kTripleTail]

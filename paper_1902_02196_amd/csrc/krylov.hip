@@ -834,13 +834,11 @@ void launch_update_triple(C<R>* w, const C<R>* Vb, long long ldv, int nvec, cons
 // and the coefficients of the stored vectors, tc[8 s ..]: (R11, R22), R12,
 // R13, R23, (1 / R11, 1 / R22), a21 = R12 / R11, b31 = R13 / R11, b32 =
 // R23 / R22 (zero where a pivot is not positive)
-__global__ void __launch_bounds__(64) k_triple_coef(double2* __restrict__ tc, const double* __restrict__ gpart,
-                                                    int nblocks) {
-    const int r = blockIdx.x, lane = threadIdx.x;
+__device__ __forceinline__ void triple_coef(double2* o, const double* __restrict__ gpart, int nblocks, int lane) {
     double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll 4
     for (int b = lane; b < nblocks; b += 64) {
-        const double* p = gpart + ((long long)r * nblocks + b) * 8;
+        const double* p = gpart + (long long)b * 8;
 #pragma unroll
         for (int q = 0; q < 8; ++q) a[q] += p[q];
     }
@@ -854,7 +852,6 @@ __global__ void __launch_bounds__(64) k_triple_coef(double2* __restrict__ tc, co
         const double d22 = g22 - (r12.x * r12.x + r12.y * r12.y);
         const double r22 = d22 > 0 ? sqrt(d22) : 0.0, i22 = r22 > 0 ? 1.0 / r22 : 0.0;
         const double2 r23 = cscale(csub(g23, cmulc(r12, r13)), i22);   // (G23 - conj(R12) R13) / R22
-        double2* o = tc + 8 * r;
         o[0] = make_double2(r11, r22);
         o[1] = r12;
         o[2] = r13;
@@ -866,18 +863,21 @@ __global__ void __launch_bounds__(64) k_triple_coef(double2* __restrict__ tc, co
     }
 }
 
-void launch_triple_coef(double2* tc, const double* gpart, int nblocks, int nrhs, hipStream_t s) {
-    hipLaunchKernelGGL(k_triple_coef, dim3(nrhs), dim3(64), 0, s, tc, gpart, nblocks);
-    VIE_HIP(hipGetLastError());
+__global__ void __launch_bounds__(64) k_triple_coef(double2* __restrict__ tc, const double* __restrict__ gpart,
+                                                    int nblocks) {
+    triple_coef(tc + 8 * blockIdx.x, gpart + (long long)blockIdx.x * nblocks * 8, nblocks, threadIdx.x);
 }
 
 // u2 <- (y2 - a21 y1) / R11, u3 <- (y3 - b31 y1 - b32 (y2 - a21 y1)) / R22 in
 // place (y_k in slots j + 1 .. j + 3 = u1, u1 + ldv, u1 + 2 ldv), with the
-// partial sums of |u2|^2 and |u3|^2 over the stored values
-template <typename R, bool PAIR>
+// partial sums of |u2|^2 and |u3|^2 over the stored values.  COEF: each
+// workgroup forms the coefficients itself, from the same sums in the same
+// order, and the first one of a slot stores them.
+template <typename R, bool PAIR, bool COEF>
 __global__ void __launch_bounds__(kTpb) k_axpy_triple(C<R>* __restrict__ u1, long long ldv, long long n,
-                                                      long long rs, const double2* __restrict__ tc,
-                                                      double* __restrict__ np2, double* __restrict__ np3) {
+                                                      long long rs, double2* __restrict__ tc,
+                                                      const double* __restrict__ gpart, double* __restrict__ np2,
+                                                      double* __restrict__ np3) {
     using U = Unit<R, PAIR>;
     using T = typename U::T;
     __shared__ double red[kTpb / 64][2];
@@ -886,7 +886,13 @@ __global__ void __launch_bounds__(kTpb) k_axpy_triple(C<R>* __restrict__ u1, lon
     T* b = reinterpret_cast<T*>(u1 + r * rs + ldv);
     T* c = reinterpret_cast<T*>(u1 + r * rs + 2 * ldv);
     const long long nu = n / U::per;
-    const double2* t = tc + 8 * r;
+    __shared__ double2 ts[8];
+    if constexpr (COEF) {   // gridDim.x is the partials' workgroup count
+        if (threadIdx.x < 64) triple_coef(ts, gpart + (long long)r * gridDim.x * 8, gridDim.x, threadIdx.x);
+        __syncthreads();
+        if (blockIdx.x == 0 && threadIdx.x < 8) tc[8 * r + threadIdx.x] = ts[threadIdx.x];
+    }
+    const double2* t = COEF ? ts : tc + 8 * r;
     const double i11 = t[4].x, i22 = t[4].y;
     const double2 a21 = t[5], b31 = t[6], b32 = t[7];
     double s2 = 0.0, s3 = 0.0;
@@ -924,15 +930,19 @@ __global__ void __launch_bounds__(kTpb) k_axpy_triple(C<R>* __restrict__ u1, lon
     }
 }
 
+// Coefficients in a launch of their own above this many partials (a workgroup
+// of the short pass reads them all, 64 bytes each): up to 256, 16^3 in
+// complex128, 4.5 us against 3.4 + 2.6 in two launches.
+constexpr int kCoefBlocks = 256;
+
 template <typename R>
-void launch_axpy_triple(C<R>* u1, long long ldv, long long n, long long rs, const double2* tc, double* np2,
-                        double* np3, int nrhs, int nblocks, hipStream_t s) {
-    if (pair_units<R>(u1, u1, n, ldv, rs, rs))
-        hipLaunchKernelGGL((k_axpy_triple<R, true>), dim3(nblocks, nrhs), dim3(kTpb), 0, s, u1, ldv, n, rs, tc, np2,
-                           np3);
-    else
-        hipLaunchKernelGGL((k_axpy_triple<R, false>), dim3(nblocks, nrhs), dim3(kTpb), 0, s, u1, ldv, n, rs, tc, np2,
-                           np3);
+void launch_axpy_triple(C<R>* u1, long long ldv, long long n, long long rs, double2* tc, const double* gpart,
+                        double* np2, double* np3, int nrhs, int nblocks, hipStream_t s) {
+    const bool coef = nblocks <= kCoefBlocks, pair = pair_units<R>(u1, u1, n, ldv, rs, rs);
+    if (!coef) hipLaunchKernelGGL(k_triple_coef, dim3(nrhs), dim3(64), 0, s, tc, gpart, nblocks);
+    auto* k = pair ? coef ? k_axpy_triple<R, true, true> : k_axpy_triple<R, true, false>
+                   : coef ? k_axpy_triple<R, false, true> : k_axpy_triple<R, false, false>;
+    hipLaunchKernelGGL(k, dim3(nblocks, nrhs), dim3(kTpb), 0, s, u1, ldv, n, rs, tc, gpart, np2, np3);
     VIE_HIP(hipGetLastError());
 }
 
@@ -1505,8 +1515,8 @@ void launch_nonfinite(int* flag, const double2* v, long long n, hipStream_t s) {
     template void launch_update_triple<R>(C<R>*, const C<R>*, long long, int, const double2*, long long,        \
                                           const double2*, long long, long long, long long, double*, double*,     \
                                           const double*, long long, int, int, int, hipStream_t);                 \
-    template void launch_axpy_triple<R>(C<R>*, long long, long long, long long, const double2*, double*,        \
-                                        double*, int, int, hipStream_t);                                          \
+    template void launch_axpy_triple<R>(C<R>*, long long, long long, long long, double2*, const double*,         \
+                                        double*, double*, int, int, hipStream_t);                                 \
     template void launch_scale_into<R>(C<R>*, const C<R>*, const double*, long long, long long, long long, int, \
                                        hipStream_t);                                                             \
     template void launch_combine<R>(double2*, const C<R>*, long long, int, const double2*, long long, long long, \

@@ -240,10 +240,9 @@ static int run(Ctx& c, const vie_solve_opts& o, int nrhs, double2* x, const Layo
                 launch_update_triple<R>(w1, Vb, ldv, nvec, L.coef3, gst, L.g3, n, n, n, L.npart, L.gpart, L.ivn, ivld,
                                         j, na, nb, c.stream);
             }
-            launch_triple_coef(L.tc, L.gpart, nb, na, c.stream);
             {   // reads y1..y3, writes u_{j+2}, u_{j+3}
                 ProfScope ps(c.prof, c.stream, VIE_K_GS_PAIR, vb * 5);
-                launch_axpy_triple<R>(w1, ldv, n, n, L.tc, L.npart2, L.npart3, na, nb, c.stream);
+                launch_axpy_triple<R>(w1, ldv, n, n, L.tc, L.gpart, L.npart2, L.npart3, na, nb, c.stream);
             }
             launch_triple_finish(as, L.g3, gst, L.tc, L.npart, L.npart2, L.npart3, nb, L.ivn + (j + 1), ivld, L.tail, j,
                                  na, c.stream);
