@@ -1399,49 +1399,69 @@ void launch_triple_finish(ArnoldiState st, const double2* g, long long gst, cons
 }
 
 // Back substitution R y = g for one slot per workgroup of one wave: lane l
-// keeps the right-hand side rows l, l + 64, ... (nvec <= 256); column i of R
-// updates the rows above i once y_i is known.
-constexpr int kBackRows = 4;   // rows per lane
+// keeps the right-hand side rows l, l + 64, ... (Q of them); column i of R
+// updates the rows above i once y_i is known.  Bound by latency: the columns
+// are loaded eight at a time, so that a step waits for arithmetic and not for
+// a load (42 columns 31.5 -> 10.8 us).
+constexpr int kBackRows = 4;   // rows per lane at most (nvec <= 256)
 
+template <int Q>
 __global__ void __launch_bounds__(64) k_backsolve(ArnoldiState st, const double* __restrict__ ivn,
                                                   long long ivn_ld, double2* __restrict__ y, int nvec) {
-    __shared__ double2 yl[64 * kBackRows];
+    constexpr int U = 8;
     const int s = blockIdx.x, lane = threadIdx.x, m = st.m;
     const double2* H = st.H + (long long)s * m * (m + 1);
     const double2* g = st.g + (long long)s * (m + 1);
-    double2 b[kBackRows];
+    double2 b[Q], yv[Q];
 #pragma unroll
-    for (int q = 0; q < kBackRows; ++q) {
+    for (int q = 0; q < Q; ++q) {
         const int k = lane + 64 * q;
         b[q] = k < nvec ? g[k] : make_double2(0.0, 0.0);
+        yv[q] = make_double2(0.0, 0.0);
     }
-    for (int i = nvec - 1; i >= 0; --i) {
-        const double2* Hi = H + (long long)i * (m + 1);
-        if (lane == (i & 63)) {
-            double2 bi = b[0];
+    for (int i0 = nvec - 1; i0 >= 0; i0 -= U) {
+        double2 c[U][Q];   // columns i0, i0 - 1, ...: rows up to the diagonal
 #pragma unroll
-            for (int q = 1; q < kBackRows; ++q)
-                if (q == (i >> 6)) bi = b[q];
-            const double2 d = Hi[i];
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int i = i0 - u, k = lane + 64 * q;
+                c[u][q] = k <= i ? H[(long long)i * (m + 1) + k] : make_double2(0.0, 0.0);
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 - u;
+            if (i < 0) break;
+            double2 bi = b[0], d = c[u][0];
+#pragma unroll
+            for (int q = 1; q < Q; ++q)
+                if (q == (i >> 6)) {
+                    bi = b[q];
+                    d = c[u][q];
+                }
             const double dd = d.x * d.x + d.y * d.y;
-            yl[i] = dd == 0.0 ? make_double2(0.0, 0.0) : cscale(cmulc(d, bi), 1.0 / dd);   // bi / d
-        }
-        __syncthreads();
-        const double2 yi = yl[i];
+            double2 yi = dd == 0.0 ? make_double2(0.0, 0.0) : cscale(cmulc(d, bi), 1.0 / dd);   // bi / d
+            yi = make_double2(__shfl(yi.x, i & 63, 64), __shfl(yi.y, i & 63, 64));   // of row i
 #pragma unroll
-        for (int q = 0; q < kBackRows; ++q) {
-            const int k = lane + 64 * q;
-            if (k < i) b[q] = csub(b[q], cmul(Hi[k], yi));
+            for (int q = 0; q < Q; ++q) {
+                const int k = lane + 64 * q;
+                if (k == i) yv[q] = yi;
+                if (k < i) b[q] = csub(b[q], cmul(c[u][q], yi));
+            }
         }
     }
-    __syncthreads();
-    for (int i = lane; i < nvec; i += 64) y[(long long)s * nvec + i] = cscale(yl[i], ivn[s * ivn_ld + i]);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int k = lane + 64 * q;
+        if (k < nvec) y[(long long)s * nvec + k] = cscale(yv[q], ivn[s * ivn_ld + k]);
+    }
 }
 
 void launch_backsolve(ArnoldiState st, const double* ivn, long long ivn_ld, double2* y, int nvec, int na,
                       hipStream_t s) {
     VIE_REQUIRE(nvec >= 1 && nvec <= 64 * kBackRows, VIE_EINVAL, "back substitution of 1..256 columns");
-    hipLaunchKernelGGL(k_backsolve, dim3(na), dim3(64), 0, s, st, ivn, ivn_ld, y, nvec);
+    if (nvec <= 64) hipLaunchKernelGGL(k_backsolve<1>, dim3(na), dim3(64), 0, s, st, ivn, ivn_ld, y, nvec);
+    else hipLaunchKernelGGL(k_backsolve<kBackRows>, dim3(na), dim3(64), 0, s, st, ivn, ivn_ld, y, nvec);
     VIE_HIP(hipGetLastError());
 }
 
