@@ -278,7 +278,8 @@ static int run(Ctx& c, const vie_solve_opts& o, int nrhs, double2* x, const Layo
                 run_steps();
                 return;
             }
-            const std::vector<long long> key{(long long)sizeof(R), na, m, o.reorth, two, three, j0, j1, n,
+            // nrhs places the buffers behind L.rhs, na the vectors of the basis
+            const std::vector<long long> key{(long long)sizeof(R), nrhs, na, m, o.reorth, two, three, j0, j1, n,
                                              (long long)reinterpret_cast<uintptr_t>(Vb), ldv,
                                              (long long)reinterpret_cast<uintptr_t>(L.rhs),
                                              (long long)reinterpret_cast<uintptr_t>(c.ws.p),

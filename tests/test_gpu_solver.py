@@ -368,3 +368,31 @@ def test_pwc_refinement_solve_odd_length(vie, torch, N):
         for k, i in enumerate(idx):
             err = relerr(_host(xd, k), xrefs[i])
             assert err < 1e-7, (i, err)
+
+
+def test_graphs_of_one_batch_size_are_not_replayed_for_another(vie, torch):
+    """Two batches with as many open right-hand sides each (two of two, two
+    of four beside two zero ones) run the same steps on the same vectors, but
+    keep their least-squares state at other places of the workspace: steps
+    captured in one are not replayed in the other.  Every solve has the bits
+    of the one launched step by step."""
+    N, D = (4, 4, 4), (0.005,) * 3
+    _say("graphs beside batch sizes")
+    e, s = vi.ellipsoid_phantom(N, D, 75)
+    c = vie.Context(0)
+    c.set_grid(N, D, F)
+    c.set_contrast(vox_to_lib(e), vox_to_lib(s))
+    two = _dev_batch(torch, [vi.complex_normal(930 + r, (12,) + N) for r in range(2)])
+    four = torch.cat([two, torch.zeros_like(two)])
+    opts = dict(mode=1, tol=1e-8, restart=6, max_outer=60)
+    refs = []
+    for et in (four, two):   # the larger first: the workspace keeps its address
+        refs.append(torch.empty_like(et))
+        assert c.solve(et, refs[-1], graph=0, **opts)[0] == vie.VIE_OK
+    for k in (0, 0, 0, 1, 1, 1, 0):   # plain, captured, replayed; then the other batch
+        et = (four, two)[k]
+        x = torch.full_like(et, float("nan"))
+        code, st = c.solve(et, x, graph=1, **opts)
+        _say("  %d vectors: status %d, %d steps" % (et.shape[0], code, st[0]["iterations"]))
+        assert code == vie.VIE_OK
+        assert torch.equal(x, refs[k])
