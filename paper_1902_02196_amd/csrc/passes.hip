@@ -884,6 +884,32 @@ __device__ __forceinline__ void curl_orbit_product(C<R>* yv, const C<R>* xv, con
     }
 }
 
+// The operator values of one frequency as 32-bit byte offsets from a base that
+// is uniform over the workgroup.
+template <typename R>
+struct OpColumn {
+    const C<R>* row;
+    unsigned off;
+    __device__ __forceinline__ C<R> at(int k) const {
+        return *reinterpret_cast<const C<R>*>(reinterpret_cast<const char*>(row) +
+                                              (off + (unsigned)k * (unsigned)sizeof(C<R>)));
+    }
+};
+template <typename R, int E, int OX>
+__device__ __forceinline__ void orbit_column(C<R>* yv, const C<R>* xv, const OpColumn<R>& u) {
+    if constexpr (E < 60) {
+        orbit_apply<R, E, 0>(yv, xv, u.at(E * OX));
+        orbit_column<R, E + 1, OX>(yv, xv, u);
+    }
+}
+template <typename R, int E, int OX>
+__device__ __forceinline__ void curl_orbit_column(C<R>* yv, const C<R>* xv, const OpColumn<R>& u) {
+    if constexpr (E < 30) {
+        curl_orbit_apply<R, E, 0>(yv, xv, u.at(E * OX));
+        curl_orbit_column<R, E + 1, OX>(yv, xv, u);
+    }
+}
+
 constexpr int kP3JmThreads = 256;
 
 template <typename R, int N>
@@ -964,12 +990,20 @@ __global__ void __launch_bounds__(kP3JmThreads) k_p3_jm(C<R>* __restrict__ A, co
                     xt[a] = flip(at(12 - 12 * h + a, xi), mask, a);
                     yv[a] = mk<R>(0, 0);
                 }
-                curl_orbit_product<R, 0>(yv, xt, Uk, ox, OX);   // K x_other
+                // complex128: 64-bit addresses per value, to which the
+                // compiler turns the plain index once one length is left,
+                // keep fewer loads in flight (64^3: 746 us, 574 so); complex64
+                // is slower with the offsets (192: 524 us, 780 so)
+                constexpr bool OFFSETS = sizeof(R) == 8;
+                const unsigned off = (unsigned)ox * (unsigned)sizeof(C<R>);
+                if constexpr (OFFSETS) curl_orbit_column<R, 0, OX>(yv, xt, OpColumn<R>{Uk, off});
+                else curl_orbit_product<R, 0>(yv, xt, Uk, ox, OX);   // K x_other
                 C<R> f = h ? km : kj;
                 if (odd) f = mk<R>(-f.x, -f.y);
 #pragma unroll
                 for (int a = 0; a < 12; ++a) yv[a] = cmul(f, yv[a]);
-                orbit_product<R, 0>(yv, xo, Un, ox, OX);        // + N x_own
+                if constexpr (OFFSETS) orbit_column<R, 0, OX>(yv, xo, OpColumn<R>{Un, off});
+                else orbit_product<R, 0>(yv, xo, Un, ox, OX);        // + N x_own
             }
             __syncthreads();
             if (act) {
