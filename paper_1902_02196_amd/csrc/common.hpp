@@ -153,12 +153,17 @@ struct Error : std::runtime_error {
     Error(int c, const std::string& m) : std::runtime_error(m), code(c) {}
 };
 
+// the error is taken off the thread's record too: the runtime keeps it there,
+// and the next launch check (of a later call, after this one was refused for
+// memory) would report it again
 #define VIE_HIP(call)                                                                        \
     do {                                                                                     \
         hipError_t e_ = (call);                                                              \
-        if (e_ != hipSuccess)                                                                \
+        if (e_ != hipSuccess) {                                                              \
+            (void)hipGetLastError();                                                         \
             throw ::vie::Error(e_ == hipErrorOutOfMemory ? -2 : -3,                         \
                                std::string(#call) + ": " + hipGetErrorString(e_));           \
+        }                                                                                    \
     } while (0)
 
 #define VIE_REQUIRE(cond, code, msg)                                   \

@@ -130,6 +130,7 @@ int run_request(Request& q) {
         if (nc != 12 && (c = vie_set_basis(ctx, nc))) { fail(c); break; }   // the operator serves both bases
         if ((c = vie_set_contrast(ctx, q.eps.data(), q.sig.data(), 0))) { fail(c); break; }
         if (hipMalloc(&et, n * sizeof(double2)) != hipSuccess || hipMalloc(&x, n * sizeof(double2)) != hipSuccess) {
+            (void)hipGetLastError();   // not left to the worker's next request
             rc = VIE_ENOMEM;
             q.error = "device allocation of the request vectors failed";
             break;
@@ -148,6 +149,7 @@ int run_request(Request& q) {
         if (r.x_out) {
             if (hipMemcpyAsync(r.x_out, x, n * sizeof(double2), hipMemcpyDeviceToHost, s) != hipSuccess ||
                 hipStreamSynchronize(s) != hipSuccess) {
+                (void)hipGetLastError();
                 rc = VIE_EDEVICE;
                 q.error = "copy of the solution failed";
                 break;

@@ -104,3 +104,26 @@ def test_setup_beside_captured_solves(vie):
         t.join()
     assert not errors, errors
     assert all(np.array_equal(v, sols[0]) for v in sols)
+
+
+def test_grid_that_does_not_fit_leaves_the_context_usable(vie):
+    """A grid whose tensors exceed the device's memory is refused after its
+    first uploads are queued; the context then takes the next grid, with the
+    bits of a context that never saw the other."""
+    import torch
+    N, D = (5, 4, 6), (0.003, 0.004, 0.005)
+    print("grid beyond memory", flush=True)
+    a, b = vie.Context(0), vie.Context(0)
+    for _ in range(2):
+        with pytest.raises(vie.VieError) as err:
+            a.set_grid((2000, 2000, 2000), D, F)   # 7.7 TB of tensors
+        assert err.value.code == vie.VIE_ENOMEM
+    for c in (a, b):
+        c.set_grid(N, D, F)
+    assert np.array_equal(a.get_toeplitz(), b.get_toeplitz())
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.view_as_complex(torch.randn(a.vec_shape(1) + (2,), generator=g, device="cuda", dtype=torch.float64))
+    ya, yb = torch.empty_like(x), torch.empty_like(x)
+    for c, y in ((a, ya), (b, yb)):
+        c.apply(x, y, op=vie.OP_N)
+    assert torch.equal(ya, yb)
