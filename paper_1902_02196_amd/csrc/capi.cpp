@@ -169,11 +169,11 @@ int vie_set_grid(vie_ctx* ctx, int nx, int ny, int nz, double dx, double dy, dou
         c.V = (long long)nx * ny * nz;
         c.Osz = (long long)c.O[0] * c.O[1] * c.O[2];
         auto opd = std::make_shared<OperatorData>();
-        // uploads go through the context's stream and end with the assembly's
-        // synchronisation: a blocking copy would break a graph capture under
-        // way in another thread
+        // uploads go through the context's stream: a blocking copy would break
+        // a graph capture under way in another thread
         std::vector<double2> tws[3];
         std::vector<float2> tws32[3];
+        const StreamDrain drain(c.stream);
         for (int i = 0; i < 3; ++i) {
             opd->ax[i].plan = make_plan(M[i]);
             std::vector<double2>& tw = tws[i];

@@ -166,6 +166,17 @@ struct Error : std::runtime_error {
         }                                                                                    \
     } while (0)
 
+// Waits for a stream when its scope is left, by return or by exception:
+// declared after host buffers that copies queued on the stream read, so that
+// those copies end before the buffers do.
+struct StreamDrain {
+    hipStream_t s;
+    explicit StreamDrain(hipStream_t s_) : s(s_) {}
+    StreamDrain(const StreamDrain&) = delete;
+    StreamDrain& operator=(const StreamDrain&) = delete;
+    ~StreamDrain() { (void)hipStreamSynchronize(s); }
+};
+
 #define VIE_REQUIRE(cond, code, msg)                                   \
     do {                                                               \
         if (!(cond)) throw ::vie::Error((code), std::string(msg));     \

@@ -767,10 +767,19 @@ __global__ void __launch_bounds__(kSpecThreads) k_spectrum_axis(const double2* _
 void assemble_blocks(double2* out, const AssemblyTables& T, int Nx, int Ny, int Nz, hipStream_t s) {
     const FarTables F = build_far_tables(T);
     VIE_REQUIRE(F.nterm <= kFarTerms && F.npair <= kFarTerms, -1, "assembly: term table overflow");
-    AssemblyTables* dT = nullptr;
-    FarTables* dF = nullptr;
-    VIE_HIP(hipMalloc(&dT, sizeof(AssemblyTables)));
-    VIE_HIP(hipMalloc(&dF, sizeof(FarTables)));
+    struct Tables {   // released after the drain below, on every way out
+        AssemblyTables* T = nullptr;
+        FarTables* F = nullptr;
+        ~Tables() {
+            if (T) (void)hipFree(T);
+            if (F) (void)hipFree(F);
+        }
+    } dev;
+    const StreamDrain drain(s);
+    VIE_HIP(hipMalloc(&dev.T, sizeof(AssemblyTables)));
+    VIE_HIP(hipMalloc(&dev.F, sizeof(FarTables)));
+    AssemblyTables* const dT = dev.T;
+    FarTables* const dF = dev.F;
     VIE_HIP(hipMemcpyAsync(dT, &T, sizeof(AssemblyTables), hipMemcpyHostToDevice, s));
     VIE_HIP(hipMemcpyAsync(dF, &F, sizeof(FarTables), hipMemcpyHostToDevice, s));
     const long long V = (long long)Nx * Ny * Nz;
@@ -814,8 +823,6 @@ void assemble_blocks(double2* out, const AssemblyTables& T, int Nx, int Ny, int 
         VIE_HIP(hipGetLastError());
     }
     VIE_HIP(hipStreamSynchronize(s));
-    VIE_HIP(hipFree(dT));
-    VIE_HIP(hipFree(dF));
 }
 
 // reflection sign of unique entry e along an axis (same for its whole orbit)
