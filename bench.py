@@ -64,23 +64,26 @@ def kernel_source_hash():
     return h.hexdigest()[:16]
 
 
-def measured_traffic(kernel_class, workload):
+def measured_traffic(kernel_class, workload, shape):
     """HBM bytes per launch of a kernel class from the committed rocprofv3
-    counter summary (profiles/counters_<workload>.md, line 'traffic-json:'),
-    or None when there is none or the kernel sources changed since."""
+    counter summary (profiles/counters_<workload>.md, lines 'traffic-json:',
+    one per launch shape that was counted), or None when none of them is of
+    the complex64 shape that ran (it decides which kernel a class is) or the
+    kernel sources changed since."""
     path = os.path.join(ROOT, "profiles", "counters_%s.md" % workload)
     if not os.path.exists(path):
         return None
     for line in open(path):
         if line.startswith("traffic-json:"):
             d = json.loads(line.split(":", 1)[1])
-            if d.get("source_hash") != kernel_source_hash():
-                return None
+            if d.get("source_hash") != kernel_source_hash() or d.get("shape") != shape:
+                continue
             k = d.get("kernels", {}).get(kernel_class)
             if not k:
                 return None
             return k["fetch_kib"] * d["fetch_scale"] * 1024 + k["write_kib"] * d["write_scale"] * 1024
     return None
+
 
 WORKLOADS = {
     "phantom64": dict(N=(64, 64, 64), h=0.003, f=298e6, seed=190202196 + 1),
@@ -561,7 +564,7 @@ def main():
     dom = max(prof, key=lambda k: prof[k][0])
     ms, nl, by = prof[dom]
     avg_s = ms / nl * 1e-3
-    tr = measured_traffic(dom, args.workload)
+    tr = measured_traffic(dom, args.workload, tune64[0])
     hbm_achieved = (by / nl) / avg_s / 1e9
     roofline = {"bound": "hbm", "achieved": round(hbm_achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(hbm_achieved / HBM_PEAK_GBS, 4), "traffic": tr, "kernel": dom,
