@@ -1293,6 +1293,7 @@ __global__ void __launch_bounds__(64 * kColWaves * 4) k_triple_finish(
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             if (lane < 3) {   // rotations 0..j - 1: (a, b) <- (c a + z b, conj(c) b - conj(z) a)
                 const double2* l = lh + lane * rows;
                 double2* Hc = st.H + ((long long)s * m + j + lane) * (m + 1);
