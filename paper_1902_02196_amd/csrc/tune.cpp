@@ -66,6 +66,9 @@ static Tune tune_t(Ctx& c, int nrhs, double* best_ms) {
     for (int var = 0; var <= 6; ++var)
         for (int sb : {1, 2, 4}) {
             if (var >= 1 && sb != 1) continue;
+            // variants 1 to 5 exist for the compiled lengths; elsewhere their
+            // names would run the staged kernel (0) and be refused when installed
+            if (var >= 1 && var <= 5 && c.nc != 3 && !p3_ct_supported(c.M[0])) continue;
             if (c.nc == 3 && var != 1) continue;   // one x-pass kernel for the PWC basis: tiles only
             if (var == 0 && p3_ct_supported(c.M[0]) && !p3_ct_fits((int)sizeof(C<R>), c.M[0])) continue;
             if (var == 2 && !p3_quad_fits((int)sizeof(C<R>), c.M[0])) continue;

@@ -204,3 +204,22 @@ def test_curl_and_coupled_products(vie, torch, M):
             for part, r in ((y[:, :12], rj), (y[:, 12:], rm)):
                 err = ((part.to(torch.complex128) - r).norm() / r.norm()).item()
                 assert err < 50 * e, (N, dtype, err)
+
+
+@pytest.mark.parametrize("nx", [1, 2, 3, 45])
+def test_autotuned_shape_can_be_installed(vie, torch, nx):
+    """x lengths of the run-time kernel (2, 4, 6) and one of the matrix-core
+    kernel alone (90): what the autotuner returns is a shape vie_set_tuning
+    takes, and gives the product it gave."""
+    c = vie.Context(0)
+    c.set_grid((nx, 3, 4), (0.003, 0.004, 0.005), F)
+    x = _random(torch, torch.Generator(device="cuda").manual_seed(nx), c.vec_shape(2))
+    for prec, dtype in ((vie.C64, torch.complex64), (vie.C128, torch.complex128)):
+        choice, _ = c.autotune(prec, 2)
+        print("nx %d %s %s" % (nx, dtype, choice), flush=True)
+        xd = x.to(dtype).contiguous()
+        ya, yb = torch.empty_like(xd), torch.full_like(xd, float("nan"))
+        c.apply(xd, ya, op=vie.OP_N)
+        c.set_tuning(choice, prec, 2)
+        c.apply(xd, yb, op=vie.OP_N)
+        assert torch.equal(ya, yb)
