@@ -56,6 +56,25 @@ bool launch_p3_mx_jm<float>(C<float>*, const C<float>*, const C<float>*, const P
 template <>
 bool launch_p3_mx_jm<double>(C<double>*, const C<double>*, const C<double>*, const P3Params&, const C<double>*,
                              C<double>, C<double>, hipStream_t);
+// Lengths whose J-M x pass is the one with 24 rows per workgroup and one fused
+// multiply-add per entry (passes.hip); the others run the matrix-core one, 48
+// rows, where those fit LDS.  The faster one of each length, us per launch
+// (24 rows / matrix cores): complex64 64^3 (128) 308 / 341, 80 x 64 x 64 (160)
+// 559 / 527, 96 x 64 x 64 (192) 525 / 632, 128 x 64 x 64 (256) 872 / 1459,
+// 160 x 48 x 48 (320) 723 / 1114, 192 x 48 x 48 (384) 1940 / 1243, at 512 the
+// 48 rows do not fit; complex128 64^3 (128) 574 / 648.  Elsewhere the
+// matrix-core one won (complex64 48^3 (96) 188 / 133, 72 x 61 x 85 (144) 3317 /
+// 729 against the run-time kernel, complex128 32^3 (64) 188 / 59).
+#define VIE_P3_JM_LENGTHS(X) X(128) X(192) X(256) X(320) X(512)
+constexpr bool p3_jm_rows24(int es, int n) {
+    switch (n) {
+#define CASE(n_) \
+    case n_: return es == 8 || n_ == 128;
+        VIE_P3_JM_LENGTHS(CASE)
+#undef CASE
+        default: return false;
+    }
+}
 bool p3_mx_jm_fits(int es, int n);
 bool p3_jm_supported(int es, int n);   // either J-M x pass
 // x pass of the PWC basis (3 component rows per pencil, compiled lengths only)

@@ -1017,8 +1017,7 @@ __global__ void __launch_bounds__(kP3JmThreads) k_p3_jm(C<R>* __restrict__ A, co
     lds_to_rows<R, N, NT>(buf, 24, p.Nx, rowp);
 }
 
-// the lengths where this kernel is faster than the matrix-core one, or the
-// only one (xpass_jm.hip states the times)
+// for the lengths of p3_jm_rows24
 template <typename R, int N>
 static bool launch_p3_jm_n(C<R>* A, const C<R>* UN, const C<R>* UK, const P3Params& p, const C<R>* tw, C<R> kj,
                            C<R> km, hipStream_t s) {
@@ -1037,10 +1036,7 @@ static bool launch_p3_jm_n(C<R>* A, const C<R>* UN, const C<R>* UK, const P3Para
     return true;
 }
 
-bool p3_jm_supported(int es, int n) {
-    if (p3_mx_jm_fits(es, n)) return true;
-    return es == 8 ? n == 128 || n == 160 || n == 192 || n == 256 || n == 320 || n == 384 || n == 512 : n == 128;
-}
+bool p3_jm_supported(int es, int n) { return p3_mx_jm_fits(es, n) || p3_jm_rows24(es, n); }
 
 // x pass of the PWC basis (3 unknowns per voxel, the pulse functions): one
 // workgroup per (octant row, right-hand side) holds the 3 component rows of
@@ -1374,14 +1370,14 @@ bool launch_p3_jm(C<R>* A, const C<R>* UN, const C<R>* UK, const P3Params& p, co
                   hipStream_t s) {
     if (2 * p.Nx > p.plan.n) return false;
     if (launch_p3_mx_jm<R>(A, UN, UK, p, tw, kj, km, s)) return true;
-    if (p.plan.n == 128) return launch_p3_jm_n<R, 128>(A, UN, UK, p, tw, kj, km, s);
-    if constexpr (sizeof(R) == 4) switch (p.plan.n) {
-        case 160: return launch_p3_jm_n<R, 160>(A, UN, UK, p, tw, kj, km, s);
-        case 192: return launch_p3_jm_n<R, 192>(A, UN, UK, p, tw, kj, km, s);
-        case 256: return launch_p3_jm_n<R, 256>(A, UN, UK, p, tw, kj, km, s);
-        case 320: return launch_p3_jm_n<R, 320>(A, UN, UK, p, tw, kj, km, s);
-        case 384: return launch_p3_jm_n<R, 384>(A, UN, UK, p, tw, kj, km, s);
-        case 512: return launch_p3_jm_n<R, 512>(A, UN, UK, p, tw, kj, km, s);
+    switch (p.plan.n) {
+#define CASE(n_)                                                                             \
+    case n_:                                                                                 \
+        if constexpr (p3_jm_rows24((int)sizeof(C<R>), n_))                                   \
+            return launch_p3_jm_n<R, n_>(A, UN, UK, p, tw, kj, km, s);                       \
+        break;
+        VIE_P3_JM_LENGTHS(CASE)
+#undef CASE
         default: break;
     }
     return false;

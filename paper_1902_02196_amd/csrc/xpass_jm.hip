@@ -3,15 +3,10 @@
 
 namespace vie {
 
-// Lengths it takes: those whose 48 rows fit LDS, except the ones where the
-// kernel with one fused multiply-add per entry and 24 rows per workgroup is
-// faster (complex64 128: 322 us against 360 at 64^3, 192: 1174 against 1411
-// at 96^3, complex128 128: 602 against 652); at the others this one wins
-// (complex64 48^3 188 -> 133, 72 x 61 x 85 3317 -> 729, complex128 32^3
-// 188 -> 59).
+// lengths it takes: those whose 48 rows fit LDS and that are not left to the
+// 24-row kernel
 template <typename R, int N> constexpr bool jm_fits() {
-    constexpr bool vec = sizeof(R) == 4 ? N == 128 || N == 160 || N == 192 || N == 256 || N >= 320 : N == 128;
-    return !vec && p3_mx_lds<R, N>(2) <= 160 * 1024;
+    return !p3_jm_rows24((int)sizeof(C<R>), N) && p3_mx_lds<R, N>(2) <= 160 * 1024;
 }
 
 bool p3_mx_jm_fits(int es, int n) {

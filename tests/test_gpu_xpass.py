@@ -223,3 +223,37 @@ def test_autotuned_shape_can_be_installed(vie, torch, nx):
         c.set_tuning(choice, prec, 2)
         c.apply(xd, yb, op=vie.OP_N)
         assert torch.equal(ya, yb)
+
+
+@pytest.mark.parametrize("M", [320, 384, 512])
+def test_coupled_products_of_long_rows(vie, torch, M):
+    """The coupled sums of the J-M product (A x, complex64) at the lengths
+    above 256 that have a kernel, full and ragged rows."""
+    w = 2 * np.pi * F
+    ce, cm = 1j * w * 8.8541878128e-12, 1j * w * 1.25663706212e-6
+    dv = 0.003 * 0.004 * 0.005
+    for N in ((M // 2, 3, 2), (M // 2 - 3, 2, 3)):
+        g = torch.Generator(device="cuda").manual_seed(M)
+        c = vie.Context(0)
+        c.set_basis(24)
+        c.set_grid(N, (0.003, 0.004, 0.005), F, fft_size=(M, 2 * N[1], 2 * N[2]))
+        T = torch.from_numpy(c.get_toeplitz()).cuda()
+        TK = torch.from_numpy(c.get_curl_toeplitz()).cuda()
+        G = torch.tensor([dv, dv / 12, dv / 12, dv / 12] * 3, device="cuda", dtype=torch.float64).view(1, 12, 1, 1, 1)
+        x = _random(torch, g, c.vec_shape(2)).to(torch.complex64)
+        x[:, 12:] *= 1e-3   # magnetic currents are of another size: both couplings count
+        shape = x.shape[2:]
+        eps, sig, mu, mi = (torch.rand(shape, generator=g, device="cuda", dtype=torch.float64) for _ in range(4))
+        eps, mu = 1 + 40 * eps, 1 + 2 * mu
+        c.set_contrast(eps, sig)
+        c.set_magnetic_contrast(mu.cpu().numpy(), mi.cpu().numpy())
+        er, mr = torch.complex(eps, -sig / (w * 8.8541878128e-12)), torch.complex(mu, -mi)
+        print("M %d N %s J-M" % (M, N), flush=True)
+        y = torch.full_like(x, float("nan"))
+        c.apply(x, y, op=vie.OP_A)
+        xj, xm = x[:, :12].to(torch.complex128), x[:, 12:].to(torch.complex128)
+        rj = er * G * xj - (er - 1) * (reference(torch, T, xj) - ce * curl_reference(torch, TK, xm))
+        rm = mr * G * xm - (mr - 1) * (reference(torch, T, xm) + cm * curl_reference(torch, TK, xj))
+        for part, r in ((y[:, :12], rj), (y[:, 12:], rm)):
+            err = ((part.to(torch.complex128) - r).norm() / r.norm()).item()
+            assert err < 50 * 6e-8, (N, err)
