@@ -408,7 +408,9 @@ int vie_autotune(vie_ctx* ctx, int precision, int nrhs, int* choice, double* bes
  * LDS, fft length <= 128 along x, 4 as 1 with two threads per frequency,
  * 5 the pencils of two right-hand sides per workgroup, 6 the block product
  * on the matrix cores, fft lengths along x of 8 ... 256 made of 2, 3 and 5
- * and 320, 384, 512 whose 24 rows fit LDS),
+ * and 320, 384, 512 whose 24 rows fit LDS; in complex128 240 and 250 are
+ * taken here, but no variant of the product runs them: vie_apply returns
+ * VIE_EINVAL),
  * workgroups per row (1, 2, 4; variant 0),
  * z tile, y tile (pencils per workgroup of the strided passes: 8 or 16, or
  * 32 where the fft length has a compiled kernel; lengths with one kernel run

@@ -213,7 +213,7 @@ void apply_op(Ctx& c, int op, int nrhs, const C<R>* x, C<R>* y, const C<R>* rhs,
         p3.sib_blocks = 1;
         p3.variant = tn.p3_variant;
         if (p3.variant < 0) p3.variant = p3_default_variant((int)es, Mx);
-        if (p3.variant == 6 && p3_ct_supported(Mx)) {
+        if (p3.variant == 6 && !p3_mx_left_out((int)es, Mx)) {
             g = 1;
         } else if (p3_ct_supported(Mx)) {
             // the staged variant shares the operator row among all siblings

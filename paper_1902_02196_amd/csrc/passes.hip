@@ -1348,7 +1348,8 @@ void launch_p3_curl(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, h
                 "magnetic product: fft length along x above 256");
     const size_t lds = (30 * (size_t)p.Ox + lds_pad(p.groups * 12 * p.pitch) + 2) * sizeof(C<R>);
     VIE_REQUIRE(lds <= 150 * 1024, -1, "magnetic product: x rows do not fit LDS");
-    if (launch_p3_mx_curl<R>(A, U, p, tw, s)) return;
+    if constexpr (sizeof(R) == 8)
+        if (launch_p3_mx_curl(A, U, p, tw, s)) return;
     const bool split4 = 4 * p.groups * p.plan.n <= nt;
     static std::once_flag once;
     std::call_once(once, [] {

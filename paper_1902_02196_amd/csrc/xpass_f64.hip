@@ -15,12 +15,15 @@ bool p3_mx_fits(int es, int n) {
 
 template <>
 bool launch_p3_mx<double>(C<double>* A, const C<double>* U, const P3Params& p, const C<double>* tw, hipStream_t s) {
-    if (!p3_mx_fits(16, p.plan.n) || 2 * p.Nx > p.plan.n) return false;
+    if (2 * p.Nx > p.plan.n) return false;
     switch (p.plan.n) {
-#define CASE(n_)                                          \
-    case n_:                                             \
-        launch_p3_mx_n<double, n_, X_N>(A, U, nullptr, p, tw, {}, {}, s);   \
-        return true;
+#define CASE(n_)                                                                          \
+    case n_:                                                                              \
+        if constexpr (p3_mx_lds<double, n_>() <= 160 * 1024 && !p3_mx_left_out(16, n_)) { \
+            launch_p3_mx_n<double, n_, X_N>(A, U, nullptr, p, tw, {}, {}, s);             \
+            return true;                                                                  \
+        }                                                                                 \
+        return false;
         VIE_MIX_LENGTHS(CASE)
 #undef CASE
         default: return false;
