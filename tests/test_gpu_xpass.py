@@ -257,3 +257,29 @@ def test_coupled_products_of_long_rows(vie, torch, M):
         for part, r in ((y[:, :12], rj), (y[:, 12:], rm)):
             err = ((part.to(torch.complex128) - r).norm() / r.norm()).item()
             assert err < 50 * 6e-8, (N, err)
+
+
+@pytest.mark.parametrize("N", [(16, 12, 10), (24, 20, 12), (5, 3, 6)])
+def test_matrix_core_shape_matches_oracle(vie, torch, N):
+    """Variant 6, installed explicitly, against the oracle's FFT product from
+    its own blocks, three right-hand sides (the other variants:
+    test_every_launch_shape_matches_oracle)."""
+    import vie_inputs as vi
+    from oracle import matvec, physics, toeplitz
+    from tests.layout import relerr, unique_from_full, vec_from_lib, vec_to_lib
+    D = (0.005, 0.004, 0.006)
+    T = toeplitz.toeplitz_full(N, D, physics.k0(F))
+    c = vie.Context(0)
+    c.set_grid(N, D, F)
+    c.set_toeplitz(unique_from_full(T))
+    xs = [vi.complex_normal(40 + r, (12,) + N) for r in range(3)]
+    Ch = matvec.circulant_spectrum(T, tuple(2 * n for n in N))
+    x = torch.from_numpy(np.stack([vec_to_lib(v) for v in xs]))
+    for dtype, prec, tile, tol in ((torch.complex64, vie.C64, 16, 1e-5), (torch.complex128, vie.C128, 8, 1e-11)):
+        print("N %s %s" % (N, dtype), flush=True)
+        xd = x.to("cuda", dtype)
+        y = torch.full_like(xd, float("nan"))
+        c.set_tuning(dict(variant=6, sib_blocks=1, tile_z=tile, tile_y=tile), prec, 3)
+        c.apply(xd, y, op=vie.OP_N)
+        for r in range(3):
+            assert relerr(vec_from_lib(y[r].cpu().numpy()), matvec.fft_N(Ch, xs[r])) < tol, (dtype, r)
