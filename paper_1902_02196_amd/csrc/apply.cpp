@@ -35,12 +35,20 @@ template <> const C<double>* curlspec<double>(const Ctx& c) { return c.op->UK128
 static int pick_tile(int n, size_t elem) { return strided_tile_for((int)elem, n); }
 
 // x-pass variant without autotuning: the matrix cores (6) at every length they
-// are compiled for, except where 24 rows leave too few workgroups per CU and
-// the light variant (1), with 12 rows, is level or faster: 256 (complex64
-// 251 us against 272 at 128 x 64 x 64, 897 against 1086 for four vectors;
-// complex128 547 against 563) and 192 in complex128 (449 against 473 at
-// 96 x 64 x 64).  Elsewhere 6 won by 6% (128 complex64) to 4 times (64
-// complex128).  Lengths without either: the staged run-time kernel (0).
+// are compiled for, but for two where the light variant (1), with 12 rows per
+// workgroup instead of 24, is faster: 256 (us at 128 x 64 x 64, one / four
+// vectors, 1 against 6: complex64 249 / 889 against 276 / 1085, complex128 549 /
+// 2089 against 565 / 2146) and 192 in complex128 (96 x 64 x 64: 449 / 1689
+// against 473 / 1828).  Elsewhere 6 is the faster one of the two: complex64 128
+// 105 against 112 (64^3; four vectors 458 against 527), 160 193 / 797 against
+// 222 / 867 (80 x 64 x 64), 192 205 / 817 against 236 / 906, 320 288 / 1210
+// against 349 / 1360 (160 x 48 x 48), 384 319 / 1310 against 570 / 2204, 512
+// 656 / 2683 against 884 / 3449; complex128 128 206 / 803 against 294 / 1098, 160
+// 388 / 1522 against 422 / 1585, 320 492 / 1900 against 911 / 3523, 384 548 /
+// 2084 against 1753 / 6839.  The autotuner finds others faster still: 2 at 64^3
+// (105, level), 5 for four vectors at 128 and 160 (447, 764), 4 at 320 and 512
+// in complex64 (221 / 842, 486 / 1877) and at 320 in complex128 (460 / 1756).
+// Lengths without either: the staged run-time kernel (0).
 static int p3_default_variant(int es, int n) {
     if (p3_ct_supported(n) && (n == 256 || (es == 16 && n == 192))) return 1;
     return p3_mx_fits(es, n) ? 6 : p3_ct_supported(n) ? 1 : 0;

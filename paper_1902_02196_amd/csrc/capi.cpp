@@ -109,7 +109,9 @@ void vie_destroy(vie_ctx* ctx) {
     if (!ctx) return;
     (void)hipSetDevice(ctx->c.device);
     // the null stream too: a device-wide synchronisation would break a graph
-    // capture under way in another thread
+    // capture under way in another thread.  Work left on a stream that
+    // vie_set_stream replaced still uses the buffers; each is released with
+    // hipFree, which waits for the device
     (void)hipStreamSynchronize(ctx->c.stream);
     delete ctx;
 }
@@ -774,7 +776,11 @@ int vie_footprint_bytes(int nx, int ny, int nz, int nrhs, int mode, int restart,
         b += 60 * V * 16;                 // block tensors
         b += 60 * O * (16 + 8);           // octant spectra, both precisions
         b += V * (3 * 16 + 3 * 8 + 8);    // materials
-        b += M * 16;                      // set-up circulant (reused as FFT workspace)
+        // allowance for fft lengths above 2 N, which the octant and the
+        // intermediates below do not count, and for the row padding; the
+        // set-up's own scratch (at most 256 V bytes, or 8 MiB, before any
+        // product's intermediates exist) is less than those
+        b += M * 16;
         // FFT intermediates ([B][Mz][Ny][Nx] + [B][Mz][My][Nx] = 6 n per rhs)
         const size_t fft = 6 * n * nrhs * s;
         const size_t fft128 = 6 * n * nrhs * 16;   // refinement residual in complex128

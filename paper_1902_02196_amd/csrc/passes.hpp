@@ -61,8 +61,7 @@ struct P3Params {
                                // per workgroup, 6: block product on the matrix cores
 };
 
-// workgroup size of the x pass: complex64 1024 threads (128 VGPRs each),
-// complex128 512 threads (256 VGPRs each)
+// workgroup size of the staged x pass
 template <typename R> constexpr int p3_threads() { return 512; }
 
 // LDS bytes of the x pass: operator row, twiddles, padded pencil groups

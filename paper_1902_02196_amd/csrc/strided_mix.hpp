@@ -6,12 +6,11 @@
 // Forward transforms are zero-padded (n_in <= N / 2), inverse ones cropped
 // (n_out <= N / 2).
 //
-// Bound by memory: 64^3 complex64 z, y, inverse y, inverse z 18, 33, 26 and
-// 18 us (4.2 to 5.8 TB/s), the kernels that stage the tile in LDS first and
-// last 21, 36, 30 and 18; 96 x 128 x 128 with four vectors 378, 755, 692 and
-// 384 against 463, 925, 1065 and 634; lengths that had only the run-time
-// kernel (72 x 61 x 85 with three, 180 along z) 96 and 124 against 246 and
-// 273.  Tiles of 128 bytes: half of that costs 20 to 40% (partial lines),
+// Bound by memory: 64^3 complex64 z, y, inverse y and inverse z with its
+// epilogue 15, 28, 27 and 29 us (3.7 to 5.7 TB/s); 96 x 128 x 128 with four
+// vectors 378, 755, 692 and 384, where staging the tile in LDS first and last
+// took 463, 925, 1065 and 634; lengths that had only the run-time kernel (72 x
+// 61 x 85 with three, 180 along z) 96 and 124 against 246 and 273.  Tiles of 128 bytes: half of that costs 20 to 40% (partial lines),
 // twice leaves fewer workgroups and gained nothing.  Plain instead of
 // streaming loads of the input save 8 us of the y pass at 64^3 and cost the
 // x pass 8, whose operator then leaves the Infinity Cache.
@@ -27,8 +26,11 @@
 namespace vie {
 
 // the radices of fft_mix.hpp, except that with the pencils fastest in LDS a
-// radix of 16 may come first: more loads in flight per work item (160: z and y
-// passes 70 and 137 us against 76 and 157 with 10 first, at 80^3 x 2)
+// radix of 16 may come first: more loads in flight per work item.  us of the z,
+// y, inverse y and inverse z passes, three complex64 vectors, 16 first against
+// 12 or 10: 96 (64 x 48 x 48) 26, 42, 42, 24 against 28, 42, 46, 33; 160 (64 x
+// 80 x 80) 82, 162, 148 against 92, 188, 170 (its inverse z is staged); 192 (64
+// x 96 x 96) 113, 227, 208, 138 against 115, 229, 211, 151.
 constexpr MixRadices strided_radices(int n) {
     switch (n) {
         case 96: return {{16, 6, 0}};

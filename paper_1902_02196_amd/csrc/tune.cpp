@@ -1,9 +1,8 @@
 // Autotuner for the launch shapes of the operator product: times each
 // candidate with HIP events on the context stream and keeps the fastest per
 // (precision, nrhs).  The candidates only change the work distribution (for
-// the PWC basis, only the strided passes' tiles); the
-// staged x-pass variant adds the terms of the block product in another order
-// than the other two, so results agree to rounding.
+// the PWC basis, only the strided passes' tiles); the x-pass variants add the
+// terms of the block product in different orders, so results agree to rounding.
 #include <algorithm>
 #include <vector>
 

@@ -26,19 +26,19 @@
 // reads global memory straight into its butterflies, the last one stores from
 // them.  Two barriers remain, around the product, which mixes the rows.
 //
-// What bounds it (64^3 complex64, 102-108 us for 333 MB): no single unit.
-// Every lane's operator load is an L1 access of its own (65 of 79 million, 65%
-// of its cycles), the vector units are busy 47% and the matrix cores 17% of the
-// time, LDS 28%, memory runs at 3.2 TB/s; without the operator loads 65 us,
-// without the product 48.  Tried and no faster: the loads along the
-// frequencies and a lane exchange through LDS (L1 accesses 79 -> 33 million,
-// LDS 28 -> 45%: 110-116 us), four siblings per workgroup (half the operator
-// loads, but workgroups too large to overlap: 125 us), a persistent kernel
-// that prefetches the next rows (its loads queue behind its stores: 172 us),
-// operator values ahead of the last forward pass (117 us).
-// Against the variants before it: 16^3 complex64 9.0 -> 8.3 us, 64^3 109 ->
-// 103, 48^3 84 -> 57, 96 x 128 x 128 with four vectors 3504 -> 3090;
-// complex128 16^3 19.8 -> 9.2, 32^3 92 -> 25, 64^3 294 -> 210; the lengths
+// What bounds it (64^3 complex64, 105-110 us for 333 MB): no single unit.
+// Every lane's operator load is an L1 access of its own (65 of 79 million); the
+// L1's address and data units are busy 71% and 85% of the time, the vector
+// units 46%, the matrix cores 17%, LDS 28%, memory runs at 3.1 TB/s; without
+// the operator loads 65 us, without the product 48.  Tried and no faster: the
+// loads along the frequencies and a lane exchange through LDS (L1 accesses 79
+// -> 33 million, LDS 28 -> 45%: 110-116 us), four siblings per workgroup (half
+// the operator loads, but workgroups too large to overlap: 125 us), a
+// persistent kernel that prefetches the next rows (its loads queue behind its
+// stores: 172 us), operator values ahead of the last forward pass (117 us).
+// Against the variants before it: 16^3 complex64 9.0 -> 8.3 us, 64^3 level
+// with the best of them (2, the siblings of a row in a workgroup), 48^3 84 ->
+// 57, 96 x 128 x 128 with four vectors 3504 -> 3090; complex128 16^3 19.8 -> 9.2, 32^3 92 -> 25, 64^3 294 -> 210; the lengths
 // that had only the run-time kernel 72 x 61 x 85 with three vectors 2593 ->
 // 601, complex128 45 x 50 x 37 with two 710 -> 107.
 //
@@ -47,8 +47,8 @@
 // two vectors, the whole magnetic-field product: 3059 -> 1648 us with the
 // strided passes (the staged kernel before it held a workgroup per CU and ran
 // its length's plan).  The J-M pass holds both coefficient sets of a row (48
-// rows) and applies N and K to each in one visit; p3_mx_jm_fits states where
-// it runs.
+// rows) and applies N and K to each in one visit; p3_jm_rows24 states where
+// it does not run.
 #pragma once
 
 #include <mutex>
@@ -574,11 +574,16 @@ __global__ void __launch_bounds__(64 * NW, 3) k_p3_mx(C<R>* __restrict__ A, cons
     if constexpr (!PassShape<N, 0>::LAST) row_passes<R, false, N, RW, 1>(buf, w, &in, t0, lane, store);
 }
 
-// Wavefronts of a workgroup: the count whose rounds leave the fewest lanes
-// idle, 3 (8 rows each) or 4 (6 rows each; lengths such as 90 = 10 x 9 whose
-// rounds hold 6 or 7 rows: 43 us against 55 with 3 at 45 x 50 x 37).  From
-// 160 up in complex128 LDS leaves so few workgroups that 6 wavefronts pay
-// (192: 966 us against 1137 at 96^3); below, they lose (64^3 262 us to 207).
+// Wavefronts of a workgroup: 3 (8 rows each) or 4 (6 rows each), the count
+// whose transforms leave the fewest lanes idle; the product's rounds are not
+// counted.  us in complex64 with 3 / 4 wavefronts (N / 2 x 64 x 64, one vector),
+// the choice first: 64 65 / 71, 72 74 / 83, 96 95 / 102, 128 104 / 121, 144 139 /
+// 163, 180 192 / 233, 192 205 / 247; 4 at 90 84 (95), 100 99 (112), 108 111 (116),
+// 120 112 (115), 150 165 (166).  It misses 80 (4: 79, 3: 77) and 160 (4: 194, 3:
+// 174), and where LDS holds few workgroups (N / 2 x 48 x 48): 320 288 / 252, 384
+// 320 / 285, 512 655 / 557, with 6 wavefronts 469.  From 160 up in complex128
+// LDS leaves so few that 6 are taken (192: 966 us against 1137 at 96^3); below,
+// they lose (64^3 262 us to 207).
 template <int N, int NW, int S>
 constexpr int lane_rounds() {
     if constexpr (S < 3 && PassShape<N, S < 3 ? S : 0>::RAD > 0) {
