@@ -42,20 +42,17 @@ constexpr double turn_cos(int m, int n) {
 // sin(2 pi m / n) = cos(2 pi (4 m + 3 n) / (4 n))
 constexpr double turn_sin(int m, int n) { return turn_cos(4 * (m % n) + 3 * n, 4 * n); }
 
-template <typename R, bool FWD, int RAD, bool HALF>
-__device__ __forceinline__ void dft_mix(C<R>* v);
-
 // v[n], n = B n1 + n2: length-A DFTs over n1, twiddles W^(n2 k1), length-B
-// DFTs over n2, output k1 + A k2.  HALF: v[n] = 0 for n >= A B / 2 (A even).
-template <typename R, bool FWD, int A, int B, bool HALF>
+// DFTs over n2, output k1 + A k2 (radix 9, whose factors have one in common).
+template <typename R, bool FWD, int A, int B>
 __device__ __forceinline__ void dft_ab(C<R>* v) {
     C<R> t[A * B];
 #pragma unroll
     for (int n2 = 0; n2 < B; ++n2) {
         C<R> u[A];
 #pragma unroll
-        for (int n1 = 0; n1 < (HALF ? A / 2 : A); ++n1) u[n1] = v[B * n1 + n2];
-        dft_mix<R, FWD, A, HALF>(u);
+        for (int n1 = 0; n1 < A; ++n1) u[n1] = v[B * n1 + n2];
+        dft_r<R, FWD, A>(u);
 #pragma unroll
         for (int k1 = 0; k1 < A; ++k1) {
             const R c = R(turn_cos(n2 * k1, A * B)), s = R((FWD ? -1 : 1) * turn_sin(n2 * k1, A * B));
@@ -64,19 +61,89 @@ __device__ __forceinline__ void dft_ab(C<R>* v) {
     }
 #pragma unroll
     for (int k1 = 0; k1 < A; ++k1) {
-        dft_mix<R, FWD, B, false>(t + k1 * B);
+        dft_r<R, FWD, B>(t + k1 * B);
 #pragma unroll
         for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = t[k1 * B + k2];
     }
 }
 
+// Length-A DFT (A = 2 or 4) of A / 2 inputs, u[s] or u[s] and u[s + 1 mod 4];
+// the others are zero and not read.
+template <typename R, bool FWD, int A>
+__device__ __forceinline__ void dft_run(C<R>* u, int s) {
+    if constexpr (A == 2) {
+        const C<R> x = u[s];
+        u[0] = x;
+        u[1] = s ? mk<R>(-x.x, -x.y) : x;
+    } else {
+        static_assert(A == 4, "a run of half the inputs");
+        const C<R> a = u[s], b = u[(s + 1) & 3];
+        const C<R> p = cadd(a, b), m = csub(a, b);
+        // W^(s k) (a + W^k b)
+        if (s == 0) {
+            const C<R> d = mul_mi<FWD>(b);
+            u[0] = p, u[2] = m, u[1] = cadd(a, d), u[3] = csub(a, d);
+        } else if (s == 2) {
+            const C<R> d = mul_mi<FWD>(b);
+            u[0] = p, u[2] = m, u[1] = mk<R>(-a.x - d.x, -a.y - d.y), u[3] = csub(d, a);
+        } else if (s == 3) {
+            const C<R> d = mul_mi<FWD>(a);
+            u[0] = p, u[2] = csub(b, a), u[1] = csub(b, d), u[3] = cadd(b, d);
+        } else {
+            const C<R> d = mul_mi<FWD>(a);
+            u[0] = p, u[2] = csub(b, a), u[1] = csub(d, b), u[3] = mk<R>(-b.x - d.x, -b.y - d.y);
+        }
+    }
+}
+
+// Inverse of a modulo m
+constexpr int inv_mod(int a, int m) {
+    for (int x = 1; x < m; ++x)
+        if (a % m * x % m == 1) return x;
+    return 1;
+}
+
+// A and B without a common factor: input n = (B n1 + A n2) mod A B, length-A
+// DFTs over n1 and length-B DFTs over n2, output k with k = k1 mod A and
+// k = k2 mod B (Good's prime factor algorithm).  No twiddles between the two:
+// their roundings, the same for every element and in all three axes, made a
+// complex64 product's error up to a third larger (20^3 1.57e-7 of the result
+// with radices 8 and 5, 2.07e-7 with a radix of 10 with twiddles).
+// HALF: v[n] = 0 for n >= A B / 2 (A even); those inputs are not read.
+template <typename R, bool FWD, int A, int B, bool HALF>
+__device__ __forceinline__ void dft_pfa(C<R>* v) {
+    constexpr int N = A * B, EA = B * inv_mod(B, A), EB = A * inv_mod(A, B);
+    C<R> t[N];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) {
+        C<R> u[A];
+        int s = 0;   // first of the run of inputs below N / 2
+#pragma unroll
+        for (int n1 = 0; n1 < A; ++n1) {
+            const int n = (B * n1 + A * n2) % N, before = (B * (n1 + A - 1) + A * n2) % N;
+            if (!HALF || 2 * n < N) u[n1] = v[n];
+            if (2 * n < N && 2 * before >= N) s = n1;
+        }
+        if constexpr (HALF) dft_run<R, FWD, A>(u, s);
+        else dft_r<R, FWD, A>(u);
+#pragma unroll
+        for (int k1 = 0; k1 < A; ++k1) t[k1 * B + n2] = u[k1];
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+        dft_r<R, FWD, B>(t + k1 * B);
+#pragma unroll
+        for (int k2 = 0; k2 < B; ++k2) v[(k1 * EA + k2 * EB) % N] = t[k1 * B + k2];
+    }
+}
+
 template <typename R, bool FWD, int RAD, bool HALF>
 __device__ __forceinline__ void dft_mix(C<R>* v) {
-    if constexpr (RAD == 6) dft_ab<R, FWD, 2, 3, HALF>(v);
-    else if constexpr (RAD == 9) dft_ab<R, FWD, 3, 3, false>(v);
-    else if constexpr (RAD == 10) dft_ab<R, FWD, 2, 5, HALF>(v);
-    else if constexpr (RAD == 12) dft_ab<R, FWD, 4, 3, HALF>(v);
-    else if constexpr (RAD == 15) dft_ab<R, FWD, 3, 5, false>(v);
+    if constexpr (RAD == 6) dft_pfa<R, FWD, 2, 3, HALF>(v);
+    else if constexpr (RAD == 9) dft_ab<R, FWD, 3, 3>(v);
+    else if constexpr (RAD == 10) dft_pfa<R, FWD, 2, 5, HALF>(v);
+    else if constexpr (RAD == 12) dft_pfa<R, FWD, 4, 3, HALF>(v);
+    else if constexpr (RAD == 15) dft_pfa<R, FWD, 3, 5, false>(v);
     else if constexpr (HALF) dft_r_halfin<R, FWD, RAD>(v);
     else dft_r<R, FWD, RAD>(v);
 }
@@ -85,7 +152,9 @@ __device__ __forceinline__ void dft_mix(C<R>* v) {
 // radix first lets a zero-padded transform skip its zero half, an even one
 // last lets a cropped inverse skip the half that is dropped; lengths that are
 // no power of two start with a radix that is no multiple of 8, so that the
-// first pass's stores, RAD elements apart, spread over the LDS banks.
+// first pass's stores, RAD elements apart, spread over the LDS banks; but 40 is
+// 8 x 5, whose twiddles' roundings add up to less than those of 10 x 4 (error
+// of a complex64 product at 20^3 1.58e-7, 1.80e-7; x pass 9.4 us, 10.2).
 struct MixRadices {
     int r[3];
 };
@@ -101,7 +170,7 @@ constexpr MixRadices mix_radices(int n) {
         case 30: return {{10, 3, 0}};
         case 32: return {{8, 4, 0}};
         case 36: return {{6, 6, 0}};
-        case 40: return {{10, 4, 0}};
+        case 40: return {{8, 5, 0}};
         case 48: return {{6, 8, 0}};
         case 50: return {{10, 5, 0}};
         case 54: return {{6, 9, 0}};

@@ -28,11 +28,13 @@ namespace vie {
 // the radices of fft_mix.hpp, except that with the pencils fastest in LDS a
 // radix of 16 may come first: more loads in flight per work item.  us of the z,
 // y, inverse y and inverse z passes, three complex64 vectors, 16 first against
-// 12 or 10: 96 (64 x 48 x 48) 26, 42, 42, 24 against 28, 42, 46, 33; 160 (64 x
-// 80 x 80) 82, 162, 148 against 92, 188, 170 (its inverse z is staged); 192 (64
-// x 96 x 96) 113, 227, 208, 138 against 115, 229, 211, 151.
+// 12 or 10: 80 (40^3, four vectors) 19, 39, 34, 19 against 19, 40, 36, 24; 96
+// (64 x 48 x 48) 26, 42, 42, 24 against 28, 42, 46, 33; 160 (64 x 80 x 80) 82,
+// 162, 148 against 92, 188, 170 (its inverse z is staged); 192 (64 x 96 x 96)
+// 113, 227, 208, 138 against 115, 229, 211, 151.
 constexpr MixRadices strided_radices(int n) {
     switch (n) {
+        case 80: return {{16, 5, 0}};
         case 96: return {{16, 6, 0}};
         case 160: return {{16, 10, 0}};
         case 192: return {{16, 12, 0}};
