@@ -32,8 +32,17 @@ namespace vie {
 // (64 x 48 x 48) 26, 42, 42, 24 against 28, 42, 46, 33; 160 (64 x 80 x 80) 82,
 // 162, 148 against 92, 188, 170 (its inverse z is staged); 192 (64 x 96 x 96)
 // 113, 227, 208, 138 against 115, 229, 211, 151.
+// 8 to 16 take two passes where one radix would do: with a whole pencil per
+// work item a workgroup of 64 had 8 or 16 of them, and the epilogue, which
+// loads and stores three values per output, waited on each in turn (64 x 64 x
+// 8, four vectors: inverse z pass 20 us in one pass, 10 in two; complex128 76
+// and 24, 33 in the staged kernel).
 constexpr MixRadices strided_radices(int n) {
     switch (n) {
+        case 8: return {{4, 2, 0}};
+        case 10: return {{2, 5, 0}};
+        case 12: return {{4, 3, 0}};
+        case 16: return {{4, 4, 0}};
         case 80: return {{16, 5, 0}};
         case 96: return {{16, 6, 0}};
         case 160: return {{16, 10, 0}};
