@@ -49,8 +49,26 @@ static int pick_tile(int n, size_t elem) { return strided_tile_for((int)elem, n)
 // (105, level), 5 for four vectors at 128 and 160 (447, 764), 4 at 320 and 512
 // in complex64 (221 / 842, 486 / 1877) and at 320 in complex128 (460 / 1756).
 // Lengths without either: the staged run-time kernel (0).
-static int p3_default_variant(int es, int n) {
-    if (p3_ct_supported(n) && (n == 256 || (es == 16 && n == 192))) return 1;
+//
+// Thin grids, whose few octant rows leave CUs idle, wait for one workgroup from
+// end to end, and variant 1's, with half the rows of N in LDS, is shorter.  The
+// rule takes the rows alone, so that a vector's bits do not depend on its
+// batch; it stops where four vectors lose with 1.  us, 1 against 6, one / four
+// vectors: complex64 128 8.0 / 9.2 against 10.4 / 10.7 at 25 rows, 13.4 / 35.2
+// against 17.2 / 34.3 at 289; 192 23.2 / 59.4 against 25.4 / 58.9 at 289; 320 46.0 /
+// 143 against 56.5 / 143 at 289; 160 12.2 / 23.5 against 14.9 / 23.3 at 81, 14.9 /
+// 37.5 against 18.8 / 35.6 at 169; 96 8.7 / 10.0 against 9.9 / 9.8 at 25, 9.9 / 18.3
+// against 10.3 / 15.5 at 81; 384 25.8 / 28.8 against 31.0 / 32.1 at 25, 28.5 / 68.9
+// against 32.2 / 57.9 at 81; 512 27.2 / 31.8 against 35.9 / 37.7 at 25, 32.2 / 106
+// against 37.7 / 91 at 81; complex128 128 9.1 / 11.5 against 12.7 / 13.4 at 25, 11.3
+// / 23.6 against 13.6 / 21.0 at 81; 96 9.4 / 12.2 against 11.2 / 11.9 at 25.
+// Shorter lengths, and longer ones in complex128, run 6 at any size.
+static long long p3_thin_rows(int es, int n) {
+    if (es == 16) return n == 96 || n == 128 ? 40 : 0;
+    return n == 128 || n == 192 || n == 320 ? 300 : n == 160 ? 100 : n >= 96 ? 40 : 0;
+}
+static int p3_default_variant(int es, int n, long long rows) {
+    if (p3_ct_supported(n) && (n == 256 || (es == 16 && n == 192) || rows <= p3_thin_rows(es, n))) return 1;
     return p3_mx_fits(es, n) ? 6 : p3_ct_supported(n) ? 1 : 0;
 }
 
@@ -220,7 +238,7 @@ void apply_op(Ctx& c, int op, int nrhs, const C<R>* x, C<R>* y, const C<R>* rhs,
             --g;
         p3.sib_blocks = 1;
         p3.variant = tn.p3_variant;
-        if (p3.variant < 0) p3.variant = p3_default_variant((int)es, Mx);
+        if (p3.variant < 0) p3.variant = p3_default_variant((int)es, Mx, (long long)c.O[1] * c.O[2]);
         if (p3.variant == 6 && !p3_mx_left_out((int)es, Mx)) {
             g = 1;
         } else if (p3_ct_supported(Mx)) {

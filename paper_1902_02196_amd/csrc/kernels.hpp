@@ -79,7 +79,7 @@ bool p3_jm_supported(int es, int n);   // either J-M x pass
 // x pass of the PWC basis (3 component rows per pencil, compiled lengths only)
 template <typename R>
 void launch_p3_pwc(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s);
-template <typename R, int N>   // all siblings of an octant row in one workgroup, N = 256
+template <typename R, int N>   // all siblings of an octant row in one workgroup, N = 256 and 128
 void launch_p3_pwc_rows(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s);
 // x pass of the curl operator K (U the [Oz][Oy][30][Ox] octant)
 template <typename R>

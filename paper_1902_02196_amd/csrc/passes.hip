@@ -1388,7 +1388,10 @@ template bool launch_p3_jm<float>(C<float>*, const C<float>*, const C<float>*, c
 template bool launch_p3_jm<double>(C<double>*, const C<double>*, const C<double>*, const P3Params&,
                                    const C<double>*, C<double>, C<double>, hipStream_t);
 
+template void launch_p3_pwc_rows<float, 128>(C<float>*, const C<float>*, const P3Params&, const C<float>*, hipStream_t);
 template void launch_p3_pwc_rows<float, 256>(C<float>*, const C<float>*, const P3Params&, const C<float>*, hipStream_t);
+template void launch_p3_pwc_rows<double, 128>(C<double>*, const C<double>*, const P3Params&, const C<double>*,
+                                              hipStream_t);
 template void launch_p3_pwc_rows<double, 256>(C<double>*, const C<double>*, const P3Params&, const C<double>*,
                                               hipStream_t);
 template void launch_strided<float>(bool, const C<float>*, C<float>*, const StridedPass&, long long, long long,

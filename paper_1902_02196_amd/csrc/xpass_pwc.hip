@@ -106,11 +106,20 @@ __global__ void __launch_bounds__(64) k_p3_pwc_wave(C<R>* __restrict__ A, const 
 // (128 x 64 x 64: 40.5 us against 48.8, four vectors in complex128 364 against
 // 429).  What bounds this one at 64^3: the transforms' arithmetic, about 13 us
 // at the vector units' rate, and 63 MB of memory traffic, 12 us.
+//
+// Thin grids (few octant rows) wait for one workgroup from end to end: there
+// one sibling per wavefront is taken at 96, 160 and 192, and the workgroup of a
+// whole row at 128.  As the bits differ, the rows alone decide, not the number
+// of vectors.  us, one / eight vectors, against two siblings: 96 5.8 / 6.3
+// against 6.6 / 7.1 at 25 rows, 5.7 / 9.2 against 6.6 / 8.7 at 81; 160 7.9 / 8.2
+// against 10.1 / 10.7 at 25, complex128 8.5 / 18.1 against 11.0 / 16.4 at 81; 192
+// 8.6 / 12.3 against 12.9 / 15.6 at 81, 9.6 / 27.3 against 13.7 / 27.8 at 289; 128
+// 6.4 / 8.7 against 7.4 / 10.1 at 81, 7.2 / 17.5 against 8.3 / 17.2 at 289.
 template <typename R, int N> constexpr int pwc_siblings() { return N < 320 ? 2 : 1; }
+template <int N> constexpr int pwc_thin_rows() { return N == 128 || N == 192 ? 300 : N == 96 || N == 160 ? 40 : 0; }
 
-template <typename R, int N>
+template <typename R, int N, int SB = pwc_siblings<R, N>()>
 static void launch_n(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hipStream_t s) {
-    constexpr int SB = pwc_siblings<R, N>();
     constexpr size_t lds = (size_t)3 * SB * RowLayout<R, N>::RB * sizeof(C<R>);
     static_assert(lds <= 64 * 1024, "within the LDS a kernel has without asking");
     const long long nblk = ((long long)p.Oy * p.Oz + 7) / 8 * 8 * (4 / SB) * (long long)p.nrhs;
@@ -126,7 +135,12 @@ void launch_p3_pwc(C<R>* A, const C<R>* U, const P3Params& p, const C<R>* tw, hi
 #define CASE(n_)                                                                                \
     case n_:                                                                                   \
         if constexpr (n_ == 256) return launch_p3_pwc_rows<R, n_>(A, U, p, tw, s);             \
-        else return launch_n<R, n_>(A, U, p, tw, s);
+        if constexpr (pwc_thin_rows<n_>() > 0)                                                 \
+            if (p.Oy * p.Oz <= pwc_thin_rows<n_>()) {                                          \
+                if constexpr (n_ == 128) return launch_p3_pwc_rows<R, n_>(A, U, p, tw, s);     \
+                else return launch_n<R, n_, 1>(A, U, p, tw, s);                                \
+            }                                                                                  \
+        return launch_n<R, n_>(A, U, p, tw, s);
         VIE_P3_LENGTHS(CASE)
 #undef CASE
         default: break;

@@ -283,3 +283,34 @@ def test_matrix_core_shape_matches_oracle(vie, torch, N):
         c.apply(xd, y, op=vie.OP_N)
         for r in range(3):
             assert relerr(vec_from_lib(y[r].cpu().numpy()), matvec.fft_N(Ch, xs[r])) < tol, (dtype, r)
+
+
+@pytest.mark.parametrize("M", [96, 128, 160, 192, 320, 384, 512])
+def test_default_x_pass_of_thin_and_thick_grids(vie, torch, M):
+    """Without a named shape, thin grids (few octant rows) and thicker ones run
+    different x passes at these lengths: both sides of the rules, PWL and PWC
+    in both precisions, and a vector's bits do not depend on its batch."""
+    for N in ((M // 2 - 3, 3, 2), (M // 2, 6, 10), (M // 2 - 1, 15, 16), (M // 2 - 3, 18, 20)):
+        c = vie.Context(0)
+        c.set_grid(N, (0.003, 0.004, 0.005), F, fft_size=(M, 2 * N[1], 2 * N[2]))
+        Th = c.get_toeplitz()
+        T = torch.from_numpy(Th).cuda()
+        g = torch.Generator(device="cuda").manual_seed(M)
+        x = _random(torch, g, c.vec_shape(3))
+        ref = reference(torch, T, x[:1])
+        x3 = x[:, ::4].contiguous()
+        x12 = torch.zeros_like(x[:1])
+        x12[:, ::4] = x3[:1]
+        ref3 = reference(torch, T, x12)[:, ::4]
+        for basis, v, r in ((12, x, ref), (3, x3, ref3)):
+            c.set_basis(basis)
+            for dtype, eps in ((torch.complex64, 6e-8), (torch.complex128, 1.2e-16)):
+                print("M %d N %s basis %d %s" % (M, N, basis, dtype), flush=True)
+                vd = v.to(dtype).contiguous()
+                y, one = torch.full_like(vd, float("nan")), torch.full_like(vd[:1], float("nan"))
+                c.apply(vd, y, op=vie.OP_N)
+                c.apply(vd[:1].contiguous(), one, op=vie.OP_N)
+                assert torch.equal(y[:1], one), (N, basis, dtype)
+                err = ((one.to(torch.complex128) - r).norm() / r.norm()).item()
+                # the inputs' own rounding to complex64 adds one eps
+                assert err < 51 * eps, (N, basis, dtype, err)
