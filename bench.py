@@ -108,8 +108,8 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
-# host threads the oracle may use: a GPU machine gives each GPU a share of 16
-# cores, whatever the machine's core count
+# host threads the oracle may use: a share of 16 for each GPU of a machine, so
+# that the baseline does not change with the machine's core count
 CPU_SHARE = 16
 
 
